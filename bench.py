@@ -37,7 +37,8 @@ DEVICE_KERNEL = {"gather_z": "k_gather_z", "contract_z": "k_contract_z", "contra
                  "sweep_gather_z": "k_sweep",
                  "spectral_rfft": "k_rfft_rings", "spectral_mac": "k_spectral",
                  "spectral_irfft": "k_irfft_rings", "stencil": "k_stencil",
-                 "stencil_blocked": "k_stencil_blocked", "mfma_gather_contract": "k_mfma",
+                 "stencil_blocked": "k_stencil_blocked", "stencil_walk": "k_stencil_walk",
+                 "fold_weights": "k_fold_weights", "mfma_gather_contract": "k_mfma",
                  "mfma_weights": "k_mfma_wop"}
 # The paper's wall-clock for its timed layer (App. B: one channel, batch 1,
 # axisymmetric four-node filter, theta_c = 3 pi / L, (L + 1) x 2L pixels; NVIDIA
@@ -116,6 +117,14 @@ def kernel_model(name, wl, work, es, spec=None):
         m["valu"] = 2.0 * pairs * B * Ci * Co
         m["bound"] = "hbm" if m["bytes"] / (HBM_PEAK_GBS * 1e9) > m["valu"] / (FP32_VALU_PEAK_TFLOPS * 1e12) \
             else "alu"
+    elif name == "stencil_walk":
+        # The same products on the fp32 matrix cores.
+        m["bytes"] = B * Ci * inp * es + B * Co * outp * es
+        m["mfma_f32"] = 2.0 * pairs * B * Ci * Co
+        m["bound"] = "hbm" if m["bytes"] / (HBM_PEAK_GBS * 1e9) > m["mfma_f32"] / (FP32_MFMA_PEAK_TFLOPS * 1e12) \
+            else "alu"
+    elif name == "fold_weights":
+        m.update(bound="hbm")
     elif name == "convert_y":
         # fp32 partial sums read, bf16 output written, per covered pixel.
         m.update(bytes=B * Co * outp * (4 + es), bound="hbm")
@@ -131,6 +140,9 @@ def kernel_model(name, wl, work, es, spec=None):
         if not spec:
             raise SystemExit("kernel %s needs the plan's spectral structure" % name)
         mi, mo = n_in // 2 + 1, n_out // 2 + 1
+        mf = max(mi, mo)   # bins of the psi tables: the longer ring's
+        K = getattr(wl, "K", 9)
+        folded = getattr(wl, "depthwise", False) or getattr(wl, "basis", "bilinear3x3") != "bilinear3x3"
         if name == "spectral_rfft":
             m["bytes"] = B * Ci * spec["slots"] * (n_in * es + mi * 8)
             m["valu"] = B * Ci * spec["slots"] * fft_flops(n_in)
@@ -139,13 +151,16 @@ def kernel_model(name, wl, work, es, spec=None):
             # channel read; per (psi table, frequency) its 9 values (pairs
             # mirrored about the equator share a table); per output bin: Yhat
             # written
-            m["bytes"] = (B * Ci * 8 * spec["pairs"] + 9 * 4 * spec.get("tables", spec["pairs"])) * mi \
-                + B * Co * spec["rings"] * mi * 8
-            m["valu"] = 36.0 * B * Ci * spec["pairs"] * mi
-            if not spec.get("z_mode"):
+            m["bytes"] = B * Ci * 8 * spec["pairs"] * mi + K * 4 * spec.get("tables", spec["pairs"]) * mf \
+                + B * Co * spec["rings"] * mo * 8
+            m["valu"] = 36.0 * B * Ci * spec["pairs"] * mf
+            if folded:
+                # one-channel items: W folded into the pair's rows, one complex product
+                m["valu"] = (2.0 * K + 8.0) * B * Ci * spec["pairs"] * mf
+            elif not spec.get("z_mode"):
                 # the contraction with W per output bin (the weight gradient's
                 # pass writes the planes of Z instead: Co = Ci * 9, no W)
-                m["valu"] += 36.0 * B * Ci * Co * spec["rings"] * mi
+                m["valu"] += 36.0 * B * Ci * Co * spec["rings"] * mo
         else:
             m["bytes"] = B * Co * spec["rings"] * (mo * 8 + n_out * es)
             m["valu"] = B * Co * spec["rings"] * fft_flops(n_out)

@@ -248,8 +248,9 @@ disco_status_t disco_transpose_depthwise(disco_plan_t plan, const disco_tensor_t
  * (disco_algo_t).  Same arguments, errors and results.  With the
  * axisymmetric and separable bases every variant runs the one schedule those
  * bases have (W folded into psi per call, see disco_kernel_work's "stencil"
- * row) except GATHER_THEN_CONTRACT and CONTRACT_THEN_GATHER, which return
- * UNSUPPORTED. */
+ * rows; on larger grids the rings near the poles through their DFT, which
+ * FUSED_DIRECT keeps on the direct sums) except GATHER_THEN_CONTRACT and
+ * CONTRACT_THEN_GATHER, which return UNSUPPORTED. */
 disco_status_t disco_forward_algo(disco_plan_t plan, const disco_tensor_t* x,
                                   const disco_tensor_t* w, disco_tensor_t* y, hipStream_t stream,
                                   int32_t algo);
@@ -382,10 +383,11 @@ int32_t disco_debug_bounds_violations(void);
  * distinct input pixels it reads; pairs[i], the non-zero (output pixel,
  * input pixel, k) triples of the sparse tensor (Sec. 4.1 eq. 7, of the
  * forward or the transposed op) whose products it accounts for (for the
- * "stencil" and "stencil_blocked" rows of the axisymmetric and separable
+ * "stencil", "stencil_blocked" and "stencil_walk" rows of the axisymmetric and separable
  * bases, whose psi has W folded in, the (output pixel, input pixel) pairs
  * instead; with these two bases a depthwise call runs the rows of
- * c_in = c_out = 1 once per channel).  A kernel
+ * c_in = c_out = 1 once per channel, and the rows are those of a call of
+ * eight items or more).  A kernel
  * that only moves intermediate data reports zeros where it touches neither
  * x nor y.  Up to `capacity` rows are written (any output pointer may be
  * NULL) and *count receives the number of kernels.  Host only, no device

@@ -191,6 +191,8 @@ disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
     if ((s = upload_vec(S.tw, &d->tw, &d->bytes, "hipMalloc(twiddles)")) != DISCO_OK) return s;
     d->N = S.N;
     d->M = S.M;
+    d->Mi = S.Ni / 2;
+    d->Mo = S.No / 2;
     d->n_rings = (int)S.rings.size();
     d->n_pairs = (int)S.pair_slot.size();
     d->n_slots = (int)S.slot_ring.size();
@@ -287,7 +289,7 @@ void free_sweep(SweepDev* d) {
     *d = SweepDev{};
 }
 
-disco_status_t pack_stencil_host(const HostOp& h, StencilHost* H) {
+disco_status_t pack_stencil_host(const HostOp& h, const std::vector<uint8_t>& heavy, StencilHost* H) {
     // Entries per work item: enough workgroups (items x longitude tiles) to
     // fill the chip several times over, within [128, 1024].
     // The tile: 512 output longitudes when a pattern has no more (two-phase
@@ -296,7 +298,7 @@ disco_status_t pack_stencil_host(const HostOp& h, StencilHost* H) {
     const int64_t n_qt = (h.g.nq + tile - 1) / tile;
     const int target = (int)std::min<int64_t>(1024, std::max<int64_t>(128, (int64_t)h.t_in.size() * n_qt / 4096));
     std::string err;
-    int rc = pack_stencil(h, target, tile, H, &err);
+    int rc = pack_stencil(h, target, tile, H, &err, heavy);
     if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
     return DISCO_OK;
 }
@@ -316,9 +318,35 @@ disco_status_t upload_stencil(const StencilHost& H, StencilDev* d) {
     P.n_items = (int32_t)H.items.size();
     P.n_split = (int32_t)H.red_pattern.size();
     P.n_slots = H.n_slots;
+    d->n_items_light = H.n_items_light;
+    d->n_split_light = H.n_split_light;
     d->tile = H.tile;
     d->n_padded = (int64_t)H.vals.size();
     return DISCO_OK;
+}
+
+disco_status_t upload_walk(const WalkHost& H, StencilDev* d) {
+    if (H.steps.empty()) return DISCO_OK;
+    disco_status_t s;
+    WalkDev& W = d->walk;
+    if ((s = upload_vec(H.steps, &W.steps, &d->bytes, "hipMalloc(ring-walk steps)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.pieces, &W.pieces, &d->bytes, "hipMalloc(ring-walk pieces)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.ring_start, &W.ring_start, &d->bytes, "hipMalloc(ring-walk rings)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.vals, &W.vals, &d->bytes, "hipMalloc(ring-walk values)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.cells, &W.cells, &d->bytes, "hipMalloc(ring-walk cells)")) != DISCO_OK) return s;
+    W.n_weights = (int32_t)H.vals.size();
+    W.pat_end = H.pat_end;
+    W.n_slots = H.n_slots;
+    W.pitch = H.pitch;
+    W.back = H.back;
+    W.ahead = H.ahead;
+    W.n_steps = (int32_t)H.steps.size();
+    return DISCO_OK;
+}
+
+int64_t walk_bytes(const WalkHost& H) {
+    if (H.steps.empty()) return 0;
+    return vec_bytes(H.steps) + vec_bytes(H.pieces) + vec_bytes(H.ring_start) + vec_bytes(H.vals) + vec_bytes(H.cells);
 }
 
 int64_t stencil_bytes(const StencilHost& H) {
@@ -375,6 +403,7 @@ struct OpTables {
     // kPartStencil (longitude stride 1): the blocked stencil layout.
     bool has_stencil = false;
     StencilHost stencil;
+    WalkHost walk;
     // kPartCore (3x3 basis): spectral rings, their flags, the general kernel
     // for the light rings, the sweep and the general kernel for the rest.
     SpectralHost sp;
@@ -421,25 +450,47 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
     // axisymmetric and separable bases, depthwise calls of any basis): the
     // general one on the packed layout, the blocked one when the longitude
     // stride is 1.  The spectral and sweep layouts are built for the 3x3 basis.
+    std::vector<uint8_t> heavy;
+    std::string err;
+    int rc = build_spectral(h, spectral_min_entries(), &T->sp, &heavy, &err, true);
+    if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
+    d->n_heavy_rings = (int32_t)T->sp.rings.size();
+    int64_t core = 0;
+    if (d->n_heavy_rings > 0) {
+        std::vector<uint8_t> light(heavy.size());
+        for (size_t i = 0; i < heavy.size(); ++i) light[i] = !heavy[i];
+        d->work_spectral = pattern_work(h, heavy);
+        d->work_light = pattern_work(h, light);
+        core += vec_bytes(T->sp.rings) + vec_bytes(T->sp.pair_ptr) + vec_bytes(T->sp.pair_slot) +
+                vec_bytes(T->sp.pair_tab) + vec_bytes(T->sp.slot_ring) + vec_bytes(T->sp.vs) + vec_bytes(T->sp.tw);
+    } else {
+        d->work_light = d->work_all;
+    }
     if (h.g.stride == 1) {
-        if ((s = pack_stencil_host(h, &T->stencil)) != DISCO_OK) return s;
+        // The wide patterns are the spectral rings, where the op has them.
+        const std::vector<uint8_t> wide = wide_patterns(h, spectral_min_entries());
+        if ((s = pack_stencil_host(h, wide, &T->stencil)) != DISCO_OK) return s;
+        rc = pack_walk(h, wide, &T->walk, &err);
+        if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
         T->has_stencil = true;
-        T->bytes[3] = stencil_bytes(T->stencil);
+        T->bytes[3] = stencil_bytes(T->stencil) + walk_bytes(T->walk);
+        d->has_walk = !T->walk.steps.empty();
+        std::vector<uint8_t> narrow(wide.size());
+        for (size_t i = 0; i < wide.size(); ++i) {
+            narrow[i] = !wide[i];
+            if (wide[i]) d->n_entries_wide += h.pat_ptr[i + 1] - h.pat_ptr[i];
+        }
+        if (d->has_walk) d->work_walk = pattern_work(h, narrow);
     }
     const CellMap cm = cell_map(h.basis);
     std::vector<int8_t> cmv(&cm.k[0][0], &cm.k[0][0] + sizeof(cm.k));
     if ((s = upload_vec(cmv, &d->cmap_dev, &d->bytes, "hipMalloc(cell map)")) != DISCO_OK) return s;
     if (h.basis != DISCO_BASIS_BILINEAR_3X3) {
-        d->work_light = d->work_all;
+        T->bytes[0] = core;
         d->tables = T;
-        d->built.store(kPartCore);  // nothing in the group for these bases
+        if (d->n_heavy_rings == 0) d->built.store(kPartCore);  // the group is the spectral tables only
         return DISCO_OK;
     }
-    std::vector<uint8_t> heavy;
-    std::string err;
-    int rc = build_spectral(h, spectral_min_entries(), &T->sp, &heavy, &err);
-    if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
-    int64_t core = 0;
     if (!T->sp.rings.empty()) {
         T->spectral_flag.assign((size_t)h.g.nlat_o, 0);
         for (int32_t r : T->sp.rings) T->spectral_flag[(size_t)r] = 1;
@@ -452,15 +503,7 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
         }
         if ((s = pack_general(h, heavy, &T->light)) != DISCO_OK) return s;
         T->has_light = true;
-        core += vec_bytes(T->sp.rings) + vec_bytes(T->sp.pair_ptr) + vec_bytes(T->sp.pair_slot) +
-                vec_bytes(T->sp.pair_tab) + vec_bytes(T->sp.slot_ring) + vec_bytes(T->sp.vs) + vec_bytes(T->sp.tw) + h.g.nlat_o +
-                packed_bytes(T->light);
-        std::vector<uint8_t> light(heavy.size());
-        for (size_t i = 0; i < heavy.size(); ++i) light[i] = !heavy[i];
-        d->work_spectral = pattern_work(h, heavy);
-        d->work_light = pattern_work(h, light);
-    } else {
-        d->work_light = d->work_all;
+        core += h.g.nlat_o + packed_bytes(T->light);
     }
     // Sweep runs over the light patterns; the rest go to the general kernel.
     rc = pack_sweep(h, kSweepTarget, heavy, &T->sw, &err);
@@ -514,13 +557,15 @@ disco_status_t upload_parts(DeviceOp* d, int parts) {
     }
     if (todo & kPartStencil) {
         if (T->has_stencil && (s = upload_stencil(T->stencil, &d->stencil)) != DISCO_OK) return s;
+        if (T->has_stencil && (s = upload_walk(T->walk, &d->stencil)) != DISCO_OK) return s;
         d->built.fetch_or(kPartStencil);
     }
     if (todo & kPartCore) {
         if (!T->sp.rings.empty()) {
             if ((s = upload_spectral(T->sp, &d->spectral)) != DISCO_OK) return s;
             int64_t b = 0;
-            if ((s = upload_vec(T->spectral_flag, &d->spectral_ring, &b, "hipMalloc(spectral ring flags)")) != DISCO_OK)
+            if (!T->spectral_flag.empty() &&
+                (s = upload_vec(T->spectral_flag, &d->spectral_ring, &b, "hipMalloc(spectral ring flags)")) != DISCO_OK)
                 return s;
             d->spectral.bytes += b;
         }
@@ -563,7 +608,9 @@ void free_op(DeviceOp* d) {
     free_sweep(&d->sweep_z);
     free_mfma(&d->mfma);
     d->mfma_state = 0;
-    void* sp[] = {d->stencil.pieces, d->stencil.chunks, d->stencil.vals, d->stencil.cells};
+    const WalkDev& W = d->stencil.walk;
+    void* sp[] = {d->stencil.pieces, d->stencil.chunks, d->stencil.vals, d->stencil.cells,
+                  W.steps, W.pieces, W.ring_start, W.vals, W.cells};
     for (void* p : sp)
         if (p) (void)hipFree(p);
     free_packed(&d->stencil.P);
@@ -615,11 +662,28 @@ struct Dispatch {
 // The small-op rule of AUTO: below 2^18 output pixel-channels one launch of
 // the general kernel over every ring (launch latency dominates), else the
 // fused schedule.
+constexpr int64_t kFoldSpectralPixels = 1 << 21;
 int32_t resolve_auto(const DeviceOp& op, int32_t algo, int64_t Co) {
     if (algo != DISCO_ALGO_AUTO) return algo;
     const double out_pix_chan = (double)Co * op.g.nlat_o * op.g.nlon_o;
     return out_pix_chan < (double)(1 << 18) ? DISCO_ALGO_FUSED_DIRECT : DISCO_ALGO_FUSED;
 }
+
+// Whether a folded-weight call of one-channel items (Ci = Co = 1, `items` of
+// them) walks the rings with narrow windows (stride-1 ops whose layout has
+// a walk), and whether the others then take the spectral path beside it
+// instead of the blocked kernel: from 2^21 output pixels on (below, the three
+// launches and the fork cost more than the polar rings' direct sums: 513 x
+// 1024, one item, 38 us without and 75 us with).  DISCO_ALGO_FUSED_DIRECT keeps the
+// direct sums everywhere.
+bool fold_walk(const DeviceOp& op, int64_t Ci, int64_t Co) { return op.has_walk && Ci == 1 && Co == 1; }
+bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
+    return fold_walk(op, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
+           items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels;
+}
+// Items assumed where a call is not at hand (plan creation, work figures):
+// a depthwise call's.
+constexpr int64_t kTypicalItems = 8;
 
 Dispatch dispatch(const DeviceOp& op, int32_t algo, int Ci, int Co, int32_t dtype) {
     const OpGeom& g = op.g;
@@ -861,10 +925,14 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
         return fail(DISCO_ERR_UNSUPPORTED, "the matrix-core kernel needs bf16 storage, the 3x3 basis, at most two "
                                            "longitude phases, stride <= 4, nlon_in a multiple of 8 and aligned x "
                                            "(16 bytes) and y (4 bytes)");
+    // The heavy rings of a folded-weight call through the spectral path (the
+    // fused schedule's own are dispatch()'s).
+    bool heavy_spectral = axisym && fold_spectral(op, algo, B, Ci, Co);
+    if (ext && heavy_spectral && !(op.built & kPartCore)) heavy_spectral = false;
     if (mfma) algo = DISCO_ALGO_MATRIX_CORE;
     if (!mfma) {
         algo = resolve_auto(op, algo, Co);
-        const int parts = needed_parts(op, algo, axisym);
+        const int parts = needed_parts(op, algo, axisym) | (heavy_spectral ? kPartCore : 0);
         if (parts & ~op.built) {
             if (ext)
                 return fail(DISCO_ERR_UNSUPPORTED, "the tables this call runs on are not on the device yet and the "
@@ -884,26 +952,46 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
                                                "call with the same shapes first");
         if ((s = ensure_parts(plan, op, kPartDirect)) != DISCO_OK) return s;
     }
-    const bool spectral = dp.spectral, sweep = dp.sweep;
-    const PackedDev& packed = axisym ? op.packed : *dp.packed;
+    bool spectral = dp.spectral, sweep = dp.sweep;
+    const PackedDev* packed_set = axisym ? &op.packed : dp.packed;
     // One output channel on a stride-1 op takes the blocked stencil kernel.
     const bool blocked = axisym && op.stencil.P.n_items > 0 && Co == 1;
+    a.walk = blocked && fold_walk(op, Ci, Co);
     size_t ws_spec = 0, ws_sweep = 0, ws = 0;
-    if (blocked) {
-        ws = workspace_bytes_fused(a, op.stencil.P);
-    } else if (axisym) {
-        ws = workspace_bytes_fused(a, packed);
-    } else if (mfma) {
-        ws = workspace_bytes_mfma(a);
-    } else if (algo == DISCO_ALGO_CONTRACT_THEN_GATHER) {
-        ws = workspace_bytes_contract_then_gather(a);
-    } else if (algo == DISCO_ALGO_GATHER_THEN_CONTRACT) {
-        ws = workspace_bytes_gather_then_contract(a);
-    } else {
-        ws_spec = spectral ? (workspace_bytes_spectral(a) + 255) / 256 * 256 : 0;
-        ws_sweep = sweep ? (workspace_bytes_sweep(a) + 255) / 256 * 256 : 0;
-        ws = ws_spec + ws_sweep + workspace_bytes_fused(a, packed);
+    auto workspace = [&] {
+        ws_spec = heavy_spectral || spectral ? (workspace_bytes_spectral(a) + 255) / 256 * 256 : 0;
+        ws_sweep = 0;
+        if (blocked) {
+            a.heavy_spectral = heavy_spectral;
+            ws = ws_spec + stencil_ws_bytes(a, op.stencil);
+        } else if (axisym) {
+            ws = workspace_bytes_fused(a, *packed_set);
+        } else if (mfma) {
+            ws = workspace_bytes_mfma(a);
+        } else if (algo == DISCO_ALGO_CONTRACT_THEN_GATHER) {
+            ws = workspace_bytes_contract_then_gather(a);
+        } else if (algo == DISCO_ALGO_GATHER_THEN_CONTRACT) {
+            ws = workspace_bytes_gather_then_contract(a);
+        } else {
+            ws_sweep = sweep ? (workspace_bytes_sweep(a) + 255) / 256 * 256 : 0;
+            ws = ws_spec + ws_sweep + workspace_bytes_fused(a, *packed_set);
+        }
+    };
+    workspace();
+    if (ext && ws > ext->bytes) {
+        // The direct kernels need less: folded-weight and two-ring-length ops
+        // run them when the transforms do not fit.
+        if (heavy_spectral) {
+            heavy_spectral = false;
+            workspace();
+        } else if (!mfma && !axisym && spectral && (op.g.P > 1 || op.g.stride > 1) && (op.built & kPartDirect)) {
+            algo = DISCO_ALGO_FUSED_DIRECT;
+            spectral = sweep = false;
+            packed_set = &op.packed;
+            workspace();
+        }
     }
+    const PackedDev& packed = *packed_set;
     if (ext && ws > ext->bytes)
         return fail(DISCO_ERR_UNSUPPORTED, "this call needs " + std::to_string(ws) + " bytes of scratch memory; the "
                     "non-allocating entry point has " + std::to_string(ext->bytes));
@@ -921,8 +1009,32 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
         e = hipMallocAsync((void**)&ws_ptr, ws, stream);
         if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(workspace)");
     }
-    if (blocked) {
-        e = launch_stencil_blocked(a, op.stencil, ws_ptr);
+    // The spectral rings (input transforms, products, inverse transforms) run
+    // on the plan's helper stream, forked from and joined back into the
+    // caller's stream, beside the direct kernels on the caller's stream; with
+    // the caller's scratch (ext) they run on its own stream instead.
+    hipEvent_t fork = nullptr, join = nullptr;
+    const bool fork_aux = (spectral || heavy_spectral) && plan->aux && !ext &&
+                          algo != DISCO_ALGO_GATHER_THEN_CONTRACT;
+    ExecArgs as = a;
+    auto spectral_rings = [&] {
+        if (!fork_aux) return launch_spectral(a, ws_ptr);
+        as.stream = plan->aux;
+        hipError_t r = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+        if (r == hipSuccess) r = hipEventCreateWithFlags(&join, hipEventDisableTiming);
+        if (r == hipSuccess) r = hipEventRecord(fork, stream);
+        if (r == hipSuccess) r = hipStreamWaitEvent(plan->aux, fork, 0);
+        if (r == hipSuccess) r = launch_spectral(as, ws_ptr);
+        return r;
+    };
+    void* direct_ws = (char*)ws_ptr + ws_spec;
+    if (heavy_spectral) {
+        e = spectral_rings();
+        if (e == hipSuccess && join) e = hipEventRecord(join, plan->aux);
+    }
+    if (e != hipSuccess) {
+    } else if (blocked) {
+        e = launch_stencil_blocked(a, op.stencil, (float*)direct_ws);
     } else if (axisym) {
         e = launch_stencil(a, packed, ws_ptr);
     } else if (mfma) {
@@ -932,36 +1044,23 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     } else if (algo == DISCO_ALGO_GATHER_THEN_CONTRACT) {
         e = launch_gather_then_contract(a, ws_ptr);
     } else {
-        // The spectral rings (input transforms, products, inverse
-        // transforms) run on the plan's helper stream, forked from and joined
-        // back into the caller's stream, beside the direct kernels on the
-        // caller's stream; when the sweep kernel takes the light rings, the
-        // general kernel's remaining rings follow the spectral ones there.
-        hipEvent_t fork = nullptr, join = nullptr;
-        const bool fork_aux = spectral && plan->aux && !ext;
-        ExecArgs as = a;
-        if (fork_aux) {
-            as.stream = plan->aux;
-            e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
-            if (e == hipSuccess) e = hipEventRecord(fork, stream);
-            if (e == hipSuccess) e = hipStreamWaitEvent(plan->aux, fork, 0);
-            if (e == hipSuccess) e = launch_spectral(as, ws_ptr, kSpectralAll);
-            if (e == hipSuccess && sweep) e = launch_fused(as, packed, (float*)((char*)ws_ptr + ws_spec + ws_sweep));
+        // When the sweep kernel takes the light rings, the general kernel's
+        // remaining rings follow the spectral ones on the helper stream.
+        float* fused_ws = (float*)((char*)direct_ws + ws_sweep);
+        if (spectral) e = spectral_rings();
+        if (e == hipSuccess && join) {
+            if (sweep) e = launch_fused(as, packed, fused_ws);
             if (e == hipSuccess) e = hipEventRecord(join, plan->aux);
-        } else if (spectral) {
-            e = launch_spectral(a, ws_ptr);
         }
-        if (e == hipSuccess && sweep) e = launch_sweep(a, ws_sweep ? (float*)((char*)ws_ptr + ws_spec) : nullptr);
-        if (e == hipSuccess && !(fork_aux && sweep))
-            e = launch_fused(a, packed, (float*)((char*)ws_ptr + ws_spec + ws_sweep));
-        if (join) {
-            hipError_t ej = hipStreamWaitEvent(stream, join, 0);
-            if (e == hipSuccess) e = ej;
-        }
-        if (fork) (void)hipEventDestroy(fork);
-        if (join) (void)hipEventDestroy(join);
+        if (e == hipSuccess && sweep) e = launch_sweep(a, ws_sweep ? (float*)direct_ws : nullptr);
+        if (e == hipSuccess && !(join && sweep)) e = launch_fused(a, packed, fused_ws);
     }
+    if (join) {
+        hipError_t ej = hipStreamWaitEvent(stream, join, 0);
+        if (e == hipSuccess) e = ej;
+    }
+    if (fork) (void)hipEventDestroy(fork);
+    if (join) (void)hipEventDestroy(join);
     hipError_t e2 = ws_ptr && !ext ? hipFreeAsync(ws_ptr, stream) : hipSuccess;
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync(workspace)");
@@ -1123,7 +1222,7 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
     const int64_t off_light = split ? (int64_t)op.cap_lo * op.g.nlon_o : 0;
     const int64_t p_light = split ? (int64_t)(op.cap_hi - op.cap_lo) * op.g.nlon_o : P;
     const int b_heavy = split ? op.spectral.n_rings * (int)B : 0;
-    const int64_t p_heavy = split ? 2 * (int64_t)(op.spectral.M + 1) : 0;
+    const int64_t p_heavy = split ? 2 * (int64_t)(op.spectral.Mo + 1) : 0;
     const size_t dyh_bytes = split ? (spectral_dyhat_bytes(za, (int)C_dy) + 255) / 256 * 256 : 0;
     const size_t gbytes = depthwise ? weight_grad_ws_bytes_dw((int)B, (int)C_x, K, P)
                           : split   ? weight_grad_split_ws_bytes((int)B, (int)C_dy, (int)(C_x * K), p_light, b_heavy, p_heavy)
@@ -1332,8 +1431,9 @@ disco_status_t disco_plan_create(int nlat_in, int nlon_in, int nlat_out, int nlo
         // sweep (two longitude phases and more than 8 input channels).
         const bool small = (double)d.g.nlat_o * d.g.nlon_o < (double)(1 << 18);
         const OpTables* T = d.tables.get();
-        const bool bare = T && T->sp.rings.empty() && (!T->has_sweep || d.g.P > 1);
-        return d.basis != DISCO_BASIS_BILINEAR_3X3 ? needed_parts(d, DISCO_ALGO_AUTO, true)
+        const bool bare = T && (d.g.P > 1 || d.g.stride > 1 || (T->sp.rings.empty() && !T->has_sweep));
+        return d.basis != DISCO_BASIS_BILINEAR_3X3 ? (needed_parts(d, DISCO_ALGO_AUTO, true) |
+                                                      (fold_spectral(d, DISCO_ALGO_AUTO, kTypicalItems, 1, 1) ? kPartCore : 0))
                                                    : (kPartCore | (small || bare ? kPartDirect : 0));
     };
     for (DeviceOp* d : {&plan->fwd, &plan->tr, &plan->fwd_adj, &plan->tr_adj})
@@ -1513,10 +1613,27 @@ disco_status_t disco_kernel_work(disco_plan_t plan, int32_t transpose, int32_t a
     } else if (op.basis != DISCO_BASIS_BILINEAR_3X3) {
         if (dp.algo != DISCO_ALGO_GATHER_THEN_CONTRACT && dp.algo != DISCO_ALGO_CONTRACT_THEN_GATHER) {
             // Folded psi: one value per (output pixel, input pixel) pair.
-            const Work fw{all.out_pixels, all.in_pixels, op.n_entries * op.g.nq};
+            const int64_t light = op.n_entries - op.n_entries_wide, nq = op.g.nq;
             const bool blocked = op.stencil.P.n_items > 0 && c_out == 1;
-            rows.push_back({blocked ? "stencil_blocked" : "stencil", fw});
-            if ((blocked ? op.stencil.P.n_split : op.packed.n_split) > 0)
+            const bool walk = blocked && fold_walk(op, c_in, c_out);
+            const bool heavy = walk && fold_spectral(op, dp.algo, kTypicalItems, c_in, c_out);
+            if (heavy) {
+                spectral_rows(op.spectral, &rows);
+                rows[1].w.pairs = op.n_entries_wide * nq;
+            }
+            if (walk) {
+                rows.push_back({"fold_weights", Work{0, 0, 0}});
+                rows.push_back({"stencil_walk", Work{op.work_walk.out_pixels, op.work_walk.in_pixels, light * nq}});
+            }
+            int n_split = blocked ? op.stencil.P.n_split : op.packed.n_split;
+            if (walk) n_split = heavy ? 0 : n_split - op.stencil.n_split_light;
+            if (!walk)
+                rows.push_back({blocked ? "stencil_blocked" : "stencil",
+                                Work{all.out_pixels, all.in_pixels, op.n_entries * nq}});
+            else if (!heavy && op.stencil.n_items_light < op.stencil.P.n_items)
+                rows.push_back({"stencil_blocked",
+                                Work{all.out_pixels - op.work_walk.out_pixels, all.in_pixels, op.n_entries_wide * nq}});
+            if (n_split > 0)
                 rows.push_back({"reduce_partials", Work{0, 0, 0}});
         }
     } else if (dp.algo == DISCO_ALGO_GATHER_THEN_CONTRACT && gather_z_split(ea)) {

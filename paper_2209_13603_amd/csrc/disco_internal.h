@@ -211,8 +211,61 @@ struct StencilHost {
     std::vector<PItem> items;
     std::vector<int32_t> red_pattern, red_ptr, red_slots;
     int32_t n_slots = 0;
+    int32_t n_items_light = 0, n_split_light = 0;  // those of the patterns not in `heavy`
 };
-int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* out, std::string* err);
+// heavy (per pattern, may be empty): patterns with wide windows.  They come
+// last, in work items and split patterns of their own, so that a launch can
+// take only them (the ring walk then has the others).
+int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* out, std::string* err,
+                 const std::vector<uint8_t>& heavy = {});
+
+// ---------------------------------------------------------------------------
+// Ring-walk layout of the folded-weight kernels (k_stencil_walk, longitude
+// stride 1, one input and one output channel per item): one wave owns
+// kWalkTile output longitudes (four per lane) of a run of steps, a step being
+// kWalkPats consecutive patterns (output rings, or longitude phases of one).
+// Input ring t lives in LDS slot t mod n_slots, columns from lag
+// ring_start[t] on, from the first step that reads it until the window
+// [lo, hi) of input rings has moved past it, so a step stages the rings new
+// to its window only.  A step's entries lie in pieces: up to kWalkLags
+// consecutive lags of one input ring from a column that is a multiple of
+// four, the step's patterns on the same lags (zeros where one has no entry).
+constexpr int kWalkTile = 256;      // output longitudes per wave
+constexpr int kWalkPats = 4;        // patterns of a step: the rows of a 4x4x1 matrix product
+constexpr int kWalkLags = 16;       // most lags of a piece: the blocks of one A operand register
+constexpr int kWalkPieces = 24;     // most pieces of a step
+constexpr int kWalkMaxPitch = 384;  // LDS columns of one slot
+constexpr int kWalkMaxFloats = 8192;  // LDS floats of all slots
+constexpr int walk_piece(int col, int lags) { return col << 5 | lags; }
+struct WStep {
+    int32_t pat;          // first pattern; the others follow (those below the last covered one)
+    int32_t lo, hi;       // input rings of the step's window
+    int32_t piece, n;     // its pieces: walk_piece(first column for lane 0, lags)
+    int32_t pad[3];
+};
+static_assert(sizeof(WStep) == 32, "WStep layout");
+struct WalkHost {
+    std::vector<WStep> steps;
+    std::vector<int32_t> pieces;
+    std::vector<int32_t> ring_start;  // per input ring: lag of column 0, mod nlon_i
+    std::vector<PVal> vals;           // per piece [kWalkLags][kWalkPats]: the entry's cell's values times q, or zeros
+    std::vector<uint8_t> cells;       // ... its cell (CellMap)
+    int32_t pat_end = 0;              // one past the last covered pattern
+    int32_t n_slots = 0, pitch = 0;
+    int32_t back = 0, ahead = 0;      // a tile at q0 stages columns of [q0 - back, q0 + ahead)
+};
+// Covers every pattern not in `wide`, if these are consecutive rings whose
+// windows fit the slots; otherwise leaves *out without steps.
+int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out, std::string* err);
+
+struct WalkDev {
+    WStep* steps = nullptr;
+    int32_t* pieces = nullptr;
+    int32_t* ring_start = nullptr;
+    PVal* vals = nullptr;
+    uint8_t* cells = nullptr;
+    int32_t n_steps = 0, n_weights = 0, pat_end = 0, n_slots = 0, pitch = 0, back = 0, ahead = 0;
+};
 
 // ---------------------------------------------------------------------------
 // Sweep layout (disco_sweep.hip): a workgroup walks a run of consecutive
@@ -290,30 +343,41 @@ struct SweepDev {
 // When an output ring's windows wrap whole input rings, its sum over one
 // input ring is a circular cross-correlation along longitude (Sec. 4.2: the
 // pattern is shift invariant), computed exactly through the discrete Fourier
-// transform:  Yhat[co][m] = sum_{t_i, ci} Xhat[t_i][ci][m]
-//   * sum_k W[co][ci][k] conj(Vhat_k[t_o, t_i][m]).
-// East-west mirror symmetry of the 3x3 basis gives Vhat_{3a+2} =
-// conj(Vhat_{3a}) and a real Vhat_{3a+1}, so each (ring pair, frequency)
-// stores 9 floats: Re/Im Vhat_{3a} and Re Vhat_{3a+1} for a = 0, 1, 2.
-// Pairs mirrored about the equator share one table (rows a = 0 and a = 2
-// exchanged), which halves the tables of an op with both polar caps.
+// transform on the finer longitude grid (N = max(nlon_i, nlon_o)):
+// Yhat[co][m] = sum_{t_i, ci} Xhat[t_i][ci][m]
+//   * sum_k W[co][ci][k] conj(Vhat_k[t_o, t_i][m]),
+// with Xhat repeated (upsampling) or Yhat folded (downsampling) between the
+// two ring lengths.  East-west mirror symmetry of every basis lets each (ring
+// pair, frequency) store K floats (rows listed in disco_spectral_plan.cpp).
+// Pairs mirrored about the equator share one table (rows exchanged), which
+// halves the tables of an op with both polar caps.
 struct SpectralHost {
-    int N = 0, M = 0;                 // ring length and M = N / 2
+    int Ni = 0, No = 0;               // input and output ring lengths (powers of two)
+    int N = 0, M = 0;                 // max(Ni, No) and M = N / 2
+    int nv = 0;                       // floats per (table, frequency): K
     std::vector<int32_t> rings;       // heavy output rings
     std::vector<int32_t> pair_ptr;    // CSR over pairs, size rings + 1
     std::vector<int32_t> pair_slot;   // input-ring slot of each pair
-    std::vector<int32_t> pair_tab;    // table of each pair in vs; bit 31: read with rows a = 0, 2 exchanged
+    std::vector<int32_t> pair_tab;    // table of each pair in vs; bit 31: read with its rows exchanged
     int32_t n_tables = 0;             // tables in vs (pairs that are no equator mirror of an earlier one)
     std::vector<int32_t> slot_ring;   // input ring of each slot
-    std::vector<float> vs;            // [table][9][M + 1], scaled by 1 / N
+    std::vector<float> vs;            // [table][nv][M + 1], scaled by 1 / N
     std::vector<float> tw;            // [N / 2][2]: exp(-2 pi i t / N)
 };
-// Fills *sp (possibly with no rings) and marks heavy patterns in *heavy.
+// Fills *sp (possibly with no rings) and marks heavy patterns in *heavy: the
+// rings whose outputs read at least min_entries (times stride^2) inputs on average, when both
+// ring lengths are powers of two from 64 to 8192.  Ops with several
+// longitude phases are covered only with `phases`.
+// The patterns of the rings with at least that many entries, whatever the
+// ring lengths.
+std::vector<uint8_t> wide_patterns(const HostOp& op, int min_entries);
 int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vector<uint8_t>* heavy,
-                   std::string* err);
+                   std::string* err, bool phases = false);
 
 struct SpectralDev {
-    int N = 0, M = 0, n_rings = 0, n_pairs = 0, n_slots = 0, n_tables = 0;
+    int N = 0, M = 0;            // the finer ring length and its half: tables, twiddles
+    int Mi = 0, Mo = 0;          // half the input and output ring lengths
+    int n_rings = 0, n_pairs = 0, n_slots = 0, n_tables = 0;
     int32_t* rings = nullptr;
     int32_t* pair_ptr = nullptr;
     int32_t* pair_slot = nullptr;
@@ -407,6 +471,8 @@ struct StencilDev {
     uint8_t* cells = nullptr;
     PackedDev P;                        // segs, items and the reduction tables (no spans)
     int32_t tile = kStencilTile;
+    int32_t n_items_light = 0, n_split_light = 0;  // the leading ones that are not heavy
+    WalkDev walk;
     int64_t n_padded = 0;
     int64_t bytes = 0;
 };
@@ -445,6 +511,7 @@ struct DeviceOp {
     PackedDev packed_rest;   // light patterns the sweep runs do not cover
     int32_t* rest_pats = nullptr;  // device: those patterns' indices (gather-then-contract schedule)
     int32_t n_rest_pats = 0;
+    int32_t n_heavy_rings = 0;   // spectral rings of the op's host tables
     uint8_t* spectral_ring = nullptr;  // device, nlat_o: 1 for output rings the spectral path writes
     // The spectral rings are exactly the polar caps [0, cap_lo) and [cap_hi,
     // nlat_o) (cap_lo < cap_hi), or cap_lo = cap_hi = 0.
@@ -452,12 +519,15 @@ struct DeviceOp {
     int32_t* pat_ptr = nullptr;  // device, n_patterns + 1
     DevEntry* entries = nullptr;  // device
     int64_t n_entries = 0;
+    int64_t n_entries_wide = 0;   // stride-1 ops: those of the wide patterns
+    bool has_walk = false;        // the stencil layout has a ring walk
     int64_t nnz_pairs = 0;
     int64_t bytes = 0;
     int64_t bytes_entries = 0;  // pat_ptr + entries (+ the cell map)
     // Work of the pattern sets above: all, spectral rings, the rest of them,
     // sweep-walked, and what the general kernel keeps beside the sweep.
     Work work_all, work_spectral, work_light, work_sweep, work_rest;
+    Work work_walk;  // the ring walk's patterns
 };
 
 // Kernel launchers (disco_kernels.hip).  All return a hipError_t.
@@ -475,6 +545,10 @@ struct ExecArgs {
     // one-channel items (B above is then B * C, Ci = Co = 1) and item i takes
     // the filter W[i mod dw_c][.] of a [C][K] weight tensor; 0 = full W.
     int dw_c = 0;
+    // The folded-weight kernels of a stride-1 op with a ring walk: its
+    // patterns through k_stencil_walk, the others through the blocked kernel
+    // (heavy_spectral: the spectral path writes those instead).
+    bool walk = false, heavy_spectral = false;
 };
 
 // The plan's device (the one that created it).
@@ -523,6 +597,9 @@ size_t workspace_bytes_fused(const ExecArgs& a, const PackedDev& P);
 // channel (a.Co = a.Ci * 9, a.w unused) instead of contracting with W.
 constexpr int kSpectralAll = 7;
 constexpr int kSpectralZ = 8;
+// One-channel items with W folded into psi (Ci = Co = 1 of the axisymmetric
+// and separable bases, depthwise calls of any basis): the products fold W
+// into the tables' rows per frequency (k_spectral_fold).
 hipError_t launch_spectral(const ExecArgs& a, float* ws, int stages = kSpectralAll);
 // Where the products' output Yhat[h][b][co][m] (M + 1 bins) lies in the
 // spectral workspace ws of launch_spectral(a, ws, ...).
@@ -549,8 +626,18 @@ hipError_t launch_reduce_partials(const ExecArgs& a, const PackedDev& P, const f
 // entry and channel pair, gathered directly into y.  Workspace as
 // launch_fused.
 hipError_t launch_stencil(const ExecArgs& a, const PackedDev& P, float* partial_ws);
-// The blocked kernel (one output channel, longitude stride 1); workspace
-// sizeof(float) * n_slots * B * nq.
+// One output channel, longitude stride 1: the blocked kernel over every
+// pattern, or with a.walk the ring walk and the blocked kernel over the rest.
+// Workspace: stencil_ws_bytes (the folded weights of the walk, then the
+// blocked kernel's partial slots).
+inline size_t walk_ws_bytes(const ExecArgs& a, const StencilDev& S) {
+    const size_t n = a.walk ? (size_t)(a.dw_c > 0 ? a.dw_c : 1) * S.walk.n_weights : 0;
+    return (sizeof(float) * n + 255) / 256 * 256;
+}
+inline size_t stencil_ws_bytes(const ExecArgs& a, const StencilDev& S) {
+    const bool partials = !(a.walk && a.heavy_spectral);
+    return walk_ws_bytes(a, S) + (partials ? sizeof(float) * (size_t)S.P.n_slots * a.B * a.op->g.nq : 0);
+}
 hipError_t launch_stencil_blocked(const ExecArgs& a, const StencilDev& S, float* partial_ws);
 
 // Weight gradient reduction (disco_grad.hip): G[m][n] = sum_{b,p} A[b][m][p]

@@ -426,7 +426,8 @@ int pack_sweep(const HostOp& op, int target_cost, const std::vector<uint8_t>& sk
 
 namespace disco {
 
-int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* out, std::string* err) {
+int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* out, std::string* err,
+                 const std::vector<uint8_t>& heavy) {
     const OpGeom& g = op.g;
     if (g.stride != 1) {
         if (err) *err = "the blocked stencil layout needs longitude stride 1";
@@ -444,7 +445,17 @@ int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* ou
         std::vector<PVal> v;
         std::vector<uint8_t> c;
     };
-    for (int pat = 0; pat < g.n_patterns(); ++pat) {
+    // Heavy patterns last.
+    std::vector<int32_t> pats;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int pat = 0; pat < g.n_patterns(); ++pat)
+            if ((!heavy.empty() && heavy[(size_t)pat]) == (pass == 1)) pats.push_back(pat);
+    int32_t seg_heavy = -1;  // first segment of a heavy pattern
+    for (int32_t pat : pats) {
+        if (seg_heavy < 0 && !heavy.empty() && heavy[(size_t)pat]) {
+            seg_heavy = (int32_t)H.segs.size();
+            H.n_split_light = (int32_t)H.red_pattern.size();
+        }
         const int32_t e0 = op.pat_ptr[(size_t)pat], e1 = op.pat_ptr[(size_t)pat + 1];
         // 1. Runs of consecutive offsets on one input ring (gaps of up to
         //    three offsets filled with zero entries), padded to whole blocks.
@@ -531,6 +542,7 @@ int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* ou
         }
         if (segs.size() > 1) H.red_ptr.push_back((int32_t)H.red_slots.size());
     }
+    if (seg_heavy < 0) H.n_split_light = (int32_t)H.red_pattern.size();
     // Work items: runs of consecutive segments with a bounded cost (entries,
     // staged columns, fixed per-segment work) and at most 64 segments.
     int acc = 0;
@@ -542,13 +554,156 @@ int pack_stencil(const HostOp& op, int target_entries, int tile, StencilHost* ou
             n += C.ent_end - C.ent_begin;
             n += (C.piece_end - C.piece_begin) * tile / 32;
         }
-        if (H.items.empty() || acc + n > target_entries || H.items.back().seg_end - H.items.back().seg_begin >= 64) {
+        if (i == seg_heavy) H.n_items_light = (int32_t)H.items.size();
+        if (H.items.empty() || i == seg_heavy || acc + n > target_entries || H.items.back().seg_end - H.items.back().seg_begin >= 64) {
             H.items.push_back(PItem{i, i + 1});
             acc = n;
         } else {
             H.items.back().seg_end = i + 1;
             acc += n;
         }
+    }
+    if (seg_heavy < 0) H.n_items_light = (int32_t)H.items.size();
+    *out = std::move(H);
+    return DISCO_OK;
+}
+
+int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out, std::string* err) {
+    *out = WalkHost{};
+    const OpGeom& g = op.g;
+    // The kernel addresses one item's planes with 32-bit byte offsets.
+    const int64_t plane = std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o);
+    if (g.stride != 1 || plane >= ((int64_t)1 << 29)) return DISCO_OK;
+    // The covered patterns: consecutive, and every one that is not wide.
+    int p0 = 0, p1 = g.n_patterns();
+    while (p0 < p1 && wide[(size_t)p0]) ++p0;
+    while (p1 > p0 && wide[(size_t)p1 - 1]) --p1;
+    for (int p = p0; p < p1; ++p)
+        if (wide[(size_t)p]) return DISCO_OK;
+    if (p0 == p1) return DISCO_OK;
+    WalkHost H;
+    H.pat_end = p1;
+    // Per step and input ring: the range of (unwrapped) lags of its patterns,
+    // and the window of input rings, made monotone over the steps.
+    struct Use { int32_t ti, dmin, dmax; };
+    std::vector<std::vector<Use>> uses;
+    std::vector<int32_t> lo, hi;
+    for (int p = p0; p < p1; p += kWalkPats) {
+        std::vector<Use> u;
+        for (int q = p; q < std::min(p + kWalkPats, p1); ++q)
+            for (int32_t e = op.pat_ptr[(size_t)q]; e < op.pat_ptr[(size_t)q + 1]; ++e) {
+                const int32_t ti = op.t_in[(size_t)e], d = op.d_raw[(size_t)e];
+                auto it = std::find_if(u.begin(), u.end(), [&](const Use& x) { return x.ti == ti; });
+                if (it == u.end()) u.push_back(Use{ti, d, d});
+                else { it->dmin = std::min(it->dmin, d); it->dmax = std::max(it->dmax, d); }
+            }
+        std::sort(u.begin(), u.end(), [](const Use& a, const Use& b) { return a.ti < b.ti; });
+        lo.push_back(u.empty() ? -1 : u.front().ti);
+        hi.push_back(u.empty() ? -1 : u.back().ti + 1);
+        uses.push_back(std::move(u));
+    }
+    const size_t ns = uses.size();
+    int32_t prev = 0;
+    for (size_t s = 0; s < ns; ++s) prev = hi[s] = std::max(prev, hi[s]);
+    prev = g.nlat_i;
+    for (size_t s = ns; s-- > 0;) prev = lo[s] = lo[s] < 0 ? prev : std::min(prev, lo[s]);
+    for (size_t s = 0; s < ns; ++s) {
+        lo[s] = std::min(lo[s], hi[s]);
+        H.n_slots = std::max(H.n_slots, hi[s] - lo[s]);
+    }
+    // Column 0 of each input ring: at or up to three lags before its first
+    // lag, the alignment that needs the fewest lags over all steps.
+    std::vector<int32_t> rmin((size_t)g.nlat_i, 0);
+    std::vector<std::vector<std::pair<int32_t, int32_t>>> ranges((size_t)g.nlat_i);
+    for (auto& u : uses)
+        for (const Use& x : u) {
+            auto& r = ranges[(size_t)x.ti];
+            rmin[(size_t)x.ti] = r.empty() ? x.dmin : std::min(rmin[(size_t)x.ti], x.dmin);
+            r.push_back({x.dmin, x.dmax});
+        }
+    H.ring_start.assign((size_t)g.nlat_i, 0);
+    for (int t = 0; t < g.nlat_i; ++t) {
+        int best = 1 << 30;
+        for (int sh = 0; sh < 4 && !ranges[(size_t)t].empty(); ++sh) {
+            const int32_t start = rmin[(size_t)t] - sh;
+            int lags = 0;
+            for (auto& r : ranges[(size_t)t]) lags += r.second - start - (r.first - start) / 4 * 4 + 1;
+            if (lags < best) { best = lags; H.ring_start[(size_t)t] = start; }
+        }
+    }
+    // Columns of a slot: a piece of n lags is read over the last lane's next
+    // (n + 6) / 4 groups of four columns.
+    for (size_t s = 0; s < ns; ++s)
+        for (const Use& x : uses[s])
+            H.pitch = std::max(H.pitch, (x.dmax - H.ring_start[(size_t)x.ti]) / 4 * 4 + kWalkTile + 4);
+    H.n_slots = std::max(H.n_slots, 1);
+    if (H.pitch > kWalkMaxPitch || H.n_slots * H.pitch > kWalkMaxFloats) return DISCO_OK;  // left to the blocked kernel
+    const std::vector<int32_t> start0 = H.ring_start;
+    for (int t = 0; t < g.nlat_i; ++t) {
+        H.back = std::max(H.back, -start0[(size_t)t]);
+        H.ahead = std::max(H.ahead, start0[(size_t)t] + H.pitch);
+    }
+    for (int32_t& d : H.ring_start) d = (d % g.nlon_i + g.nlon_i) % g.nlon_i;
+    // Pieces and weights.  A range of lags is cut into the fewest pieces, of
+    // nearly equal lengths, each starting at a multiple of four columns.
+    for (size_t s = 0; s < ns; ++s) {
+        const int p = p0 + kWalkPats * (int)s;
+        WStep S{};
+        S.pat = p;
+        S.lo = lo[s];
+        S.hi = hi[s];
+        S.piece = (int32_t)H.pieces.size();
+        struct Piece2 { int32_t ti, col, lags; };
+        std::vector<Piece2> pc;
+        for (const Use& x : uses[s]) {
+            const int32_t start = start0[(size_t)x.ti];
+            int32_t c = (x.dmin - start) / 4 * 4;
+            const int32_t end = x.dmax - start + 1;
+            while (c < end) {
+                const int32_t left = end - c, parts = (left + kWalkLags - 1) / kWalkLags;
+                int32_t len = left;
+                if (parts > 1) len = std::min(kWalkLags, (left / parts + 3) / 4 * 4);
+                pc.push_back(Piece2{x.ti, c, len});
+                c += len;
+            }
+        }
+        S.n = (int32_t)pc.size();
+        if (S.n > kWalkPieces) return DISCO_OK;  // left to the blocked kernel
+        H.vals.resize(H.vals.size() + pc.size() * kWalkPats * kWalkLags, PVal{});
+        H.cells.resize(H.vals.size(), 0);
+        for (const Piece2& b : pc) {
+            H.pieces.push_back(walk_piece(b.ti % H.n_slots * H.pitch + b.col, b.lags));
+            if (b.col + (b.lags + 3 + 3) / 4 * 4 + kWalkTile - 4 > H.pitch) {
+                if (err) *err = "internal: ring-walk columns past the slot";
+                return DISCO_ERR_DEVICE;
+            }
+        }
+        int64_t placed = 0, want = 0;
+        for (int q = p; q < std::min(p + kWalkPats, p1); ++q)
+            for (int32_t e = op.pat_ptr[(size_t)q]; e < op.pat_ptr[(size_t)q + 1]; ++e) {
+                ++want;
+                const int32_t ti = op.t_in[(size_t)e];
+                const int32_t col = op.d_raw[(size_t)e] - start0[(size_t)ti];
+                PVal pv{};
+                int cell = 0;
+                if (!entry_cell_values(op, e, &cell, pv.v)) {
+                    if (err) *err = "internal: basis value outside its hat cell";
+                    return DISCO_ERR_DEVICE;
+                }
+                for (size_t i = 0; i < pc.size(); ++i)
+                    if (pc[i].ti == ti && col >= pc[i].col && col < pc[i].col + pc[i].lags) {
+                        const size_t at = (((size_t)S.piece + i) * kWalkLags + (size_t)(col - pc[i].col)) * kWalkPats + (size_t)(q - p);
+                        H.vals[at] = pv;
+                        H.cells[at] = (uint8_t)cell;
+                        ++placed;
+                        break;
+                    }
+            }
+        if (placed != want) {
+            if (err) *err = "internal: ring-walk pieces do not hold every entry";
+            return DISCO_ERR_DEVICE;
+        }
+        H.steps.push_back(S);
     }
     *out = std::move(H);
     return DISCO_OK;

@@ -17,7 +17,17 @@
 // has no function) in LDS, and fold c = sum_m T[j][cell][m] v[m] while an
 // entry is staged.
 //
-// Layout and walk are the packed one of the fused kernel (disco_fused.hip):
+// Three kernels.  k_stencil_walk takes the one-channel items of stride-1 ops
+// on every ring with narrow windows: it keeps input rings in LDS while it
+// walks output rings.  k_stencil_blocked takes the wide rings beside it (the
+// spectral path does on larger grids) and ops with several input channels
+// and one output channel; k_stencil the rest.  Alone on one box, 2048 x
+// 4096, eight separable channels: the blocked kernel over every ring 640 us,
+// over the narrow rings 500 us, the walk over the narrow rings 183 us (512
+// MB at 2.8 TB/s; 107 us without its products, which occupy the fp32 matrix
+// cores for about 70 us).
+//
+// k_stencil's layout and walk are the packed one of the fused kernel (disco_fused.hip):
 // one workgroup = 256 consecutive output longitudes of one pattern (output
 // ring, phase) of a work item, for one batch element and a tile of COT output
 // channels.  For each input channel and each chunk of the pattern:
@@ -395,30 +405,403 @@ __global__ __launch_bounds__(TILE / 4) void k_stencil_blocked(const PItem* __res
 template <typename T, int TILE>
 hipError_t stencil_blocked_launch(const ExecArgs& a, const StencilDev& S, float* partial) {
     const OpGeom& g = a.op->g;
-    if (S.P.n_items == 0) return hipSuccess;
+    // With a ring walk only the wide patterns, whose items come last.
+    PackedDev P = S.P;
+    if (a.walk) {
+        P.items += S.n_items_light;
+        P.n_items -= S.n_items_light;
+        P.red_pattern += S.n_split_light;
+        P.red_ptr += S.n_split_light;
+        P.n_split -= S.n_split_light;
+    }
+    if (P.n_items == 0) return hipSuccess;
     const int n_qtiles = (g.nq + TILE - 1) / TILE;
-    dim3 grid((unsigned)(S.P.n_items * n_qtiles), (unsigned)a.B);
+    dim3 grid((unsigned)(P.n_items * n_qtiles), (unsigned)a.B);
     const int tk = timing_begin("stencil_blocked", a.stream);
-    hipLaunchKernelGGL((k_stencil_blocked<T, TILE>), grid, dim3(TILE / 4), 0, a.stream, S.P.items, S.P.segs,
+    hipLaunchKernelGGL((k_stencil_blocked<T, TILE>), grid, dim3(TILE / 4), 0, a.stream, P.items, P.segs,
                        S.chunks, S.pieces, S.vals, S.cells, a.op->cmap_dev, g, (const T*)a.x, (const T*)a.w,
                        (T*)a.y, partial, a.Ci, basis_size(a.op->basis), n_qtiles, a.dw_c);
     timing_end(tk, a.stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce_partials(a, S.P, partial);
+    return launch_reduce_partials(a, P, partial);
+}
+
+// The folded weights of the ring walk: fw[c][i] = sum_m W[c][map[cell][m]]
+// v[m] for every weight i and channel c (one row when dw_c is 0: Ci = Co = 1).
+// grid: (ceil(n / 256), rows)
+template <typename T>
+__global__ __launch_bounds__(256) void k_fold_weights(const PVal* __restrict__ vals, const uint8_t* __restrict__ cells,
+                                                      const int8_t* __restrict__ cmap, const T* __restrict__ w,
+                                                      float* __restrict__ fw, int n, int K) {
+    __shared__ float wt[kCells * 4];
+    const int c = blockIdx.y;
+    if (threadIdx.x < kCells * 4) {
+        const int k = cmap[threadIdx.x];
+        wt[threadIdx.x] = k >= 0 ? load_val(w, (int64_t)c * K + k) : 0.0f;
+    }
+    __syncthreads();
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const PVal v = vals[i];
+    const float4 t = *(const float4*)(wt + 4 * cells[i]);
+    fw[(int64_t)c * n + i] = t.x * v.v[0] + t.y * v.v[1] + t.z * v.v[2] + t.w * v.v[3];
+}
+
+// Raw buffer access (word 3 of the descriptor for gfx9 raw access): an offset
+// at or past num_records reads 0 and drops a store, so that a step issues the
+// same number of memory operations whatever it loads and stores, and a wait
+// for the next rings' columns does not cover the stores issued after them.
+constexpr int kRawBufferFlags = 0x00020000;
+constexpr int kBufferOutOfRange = (int)0x80000000u;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, kRawBufferFlags);
+}
+// Element i, or the four from i on, of a buffer of T (i < 0: out of range).
+__device__ __forceinline__ float buffer_load1(const float*, __amdgpu_buffer_rsrc_t r, int i) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, i < 0 ? kBufferOutOfRange : 4 * i, 0, 0));
+}
+__device__ __forceinline__ float buffer_load1(const uint16_t*, __amdgpu_buffer_rsrc_t r, int i) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, i < 0 ? kBufferOutOfRange : 2 * i, 0, 0) << 16);
+}
+__device__ __forceinline__ float4 buffer_load4(const float*, __amdgpu_buffer_rsrc_t r, int i) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, i < 0 ? kBufferOutOfRange : 4 * i, 0, 0);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+__device__ __forceinline__ void buffer_store1(float*, __amdgpu_buffer_rsrc_t r, int i, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, i < 0 ? kBufferOutOfRange : 4 * i, 0, 0);
+}
+__device__ __forceinline__ void buffer_store1(uint16_t*, __amdgpu_buffer_rsrc_t r, int i, float v) {
+    __builtin_amdgcn_raw_buffer_store_b16(to_bf16(v), r, i < 0 ? kBufferOutOfRange : 2 * i, 0, 0);
+}
+__device__ __forceinline__ void buffer_store4(float*, __amdgpu_buffer_rsrc_t r, int i, const float (&v)[4]) {
+    const u32x4 u = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    __builtin_amdgcn_raw_buffer_store_b128(u, r, i < 0 ? kBufferOutOfRange : 4 * i, 0, 0);
+}
+__device__ __forceinline__ void buffer_store4(uint16_t*, __amdgpu_buffer_rsrc_t r, int i, const float (&v)[4]) {
+    const u32x2 u = {(uint32_t)to_bf16(v[0]) | (uint32_t)to_bf16(v[1]) << 16,
+                     (uint32_t)to_bf16(v[2]) | (uint32_t)to_bf16(v[3]) << 16};
+    __builtin_amdgcn_raw_buffer_store_b64(u, r, i < 0 ? kBufferOutOfRange : 2 * i, 0, 0);
+}
+
+constexpr int kWalkLoads = (kWalkMaxPitch + 255) / 256;  // float4 columns per lane of one staged ring
+constexpr int kWalkAhead = 4;                            // rings staged one step ahead, in registers
+constexpr int kWalkW4 = kWalkPieces * kWalkPats * kWalkLags / 256;  // float4 weights per lane of a step
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// One piece in registers: the lane's columns from the piece's first one on,
+// and the folded weights as A operand (lane i + 4 b: pattern i, lag b).
+struct WalkPiece {
+    float4 v[5];
+    float w;
+    int lags;
+};
+__device__ __forceinline__ void walk_fetch(WalkPiece& P, int piece, const float* __restrict__ wl,
+                                           const float4* __restrict__ xl) {
+    P.lags = piece & 31;
+    P.w = *wl;
+    const float4* xp = xl + (piece >> 7);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) P.v[u] = xp[u];
+    if (P.lags > 5) {
+        P.v[2] = xp[2];
+        if (P.lags > 9) {
+            P.v[3] = xp[3];
+            if (P.lags > 13) P.v[4] = xp[4];
+        }
+    }
+}
+
+// acc[o][pattern] += w[pattern][j] x[o + j] for lags j = J .. lags - 1: one
+// v_mfma_f32_4x4x1_16b_f32 per lag and output o of the lanes (the A block of
+// lag j broadcast to all sixteen 4-column blocks: CBSZ = 4, ABID = j).
+template <int J>
+__device__ __forceinline__ void walk_products(const WalkPiece& P, const float (&x)[20], v4f (&acc)[4]) {
+    if constexpr (J < kWalkLags) {
+        if (J < P.lags) {
+#pragma unroll
+            for (int o = 0; o < 4; ++o) acc[o] = __builtin_amdgcn_mfma_f32_4x4x1f32(P.w, x[J + o], acc[o], 4, J, 0);
+            walk_products<J + 1>(P, x, acc);
+        }
+    }
+}
+__device__ __forceinline__ void walk_piece_products(const WalkPiece& P, v4f (&acc)[4]) {
+    const float x[20] = {P.v[0].x, P.v[0].y, P.v[0].z, P.v[0].w, P.v[1].x, P.v[1].y, P.v[1].z,
+                         P.v[1].w, P.v[2].x, P.v[2].y, P.v[2].z, P.v[2].w, P.v[3].x, P.v[3].y,
+                         P.v[3].z, P.v[3].w, P.v[4].x, P.v[4].y, P.v[4].z, P.v[4].w};
+    walk_products<0>(P, x, acc);
+}
+
+// The pieces of a step, the next one's columns and weights requested before
+// the current one's products; two register sets swap roles.  Lane i of
+// `desc` holds piece i; wl: this lane's weight of piece 0 in LDS.
+__device__ __forceinline__ void walk_pieces(int n, int desc, const float* __restrict__ wl,
+                                            const float4* __restrict__ xl, v4f (&acc)[4]) {
+    if (n == 0) return;
+    WalkPiece A, B;
+    walk_fetch(A, __builtin_amdgcn_readlane(desc, 0), wl, xl);
+    int i = 0;
+    for (; i + 1 < n; i += 2) {
+        walk_fetch(B, __builtin_amdgcn_readlane(desc, i + 1), wl + 64 * (i + 1), xl);
+        __builtin_amdgcn_sched_barrier(0);
+        walk_piece_products(A, acc);
+        const int nx = i + 2 < n ? i + 2 : i + 1;
+        walk_fetch(A, __builtin_amdgcn_readlane(desc, nx), wl + 64 * nx, xl);
+        __builtin_amdgcn_sched_barrier(0);
+        walk_piece_products(B, acc);
+    }
+    if (i < n) walk_piece_products(A, acc);
+}
+
+struct WalkArgs {
+    int n_steps, run_len, n_runs, n_tiles, n_slots, pitch, n_weights, dw_c, pat_end, back, ahead;
+};
+
+// The ring walk (layout: disco_internal.h).  One wave per workgroup: no
+// barriers, LDS ordered by the wave's own program order; lane l owns outputs
+// q0 + 4 l .. + 3 of the step's patterns.  The products run on the fp32 matrix
+// cores, four patterns by 64 outputs per instruction; as VALU FMAs the
+// weights would be scalar operands, at which the FMA rate halves.  VEC: four
+// outputs per store (P <= 2, whole lanes, aligned rows).
+enum { kColumns = 0, kInside = 1, kSeam = 2 };  // how a tile's columns are loaded
+template <typename T, bool VEC, int LOAD>
+__device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* __restrict__ steps,
+                                         const int32_t* __restrict__ pieces, const int32_t* __restrict__ ring_start,
+                                         const float* __restrict__ fw, const WalkArgs& W, const OpGeom& g,
+                                         const T* __restrict__ x, T* __restrict__ y, int item, int q0, int s0, int s1) {
+    const int lane = threadIdx.x;
+    const int pitch = W.pitch, n_slots = W.n_slots;
+    const float* wc = fw + (W.dw_c > 0 ? (int64_t)(item % W.dw_c) * W.n_weights : 0);
+    const float4* xl = xs4 + lane;
+    const int n_in = g.nlat_i * g.nlon_i, n_out = g.nlat_o * g.nlon_o;
+    const __amdgpu_buffer_rsrc_t xr = buffer_of(x + (int64_t)item * n_in, n_in * (int)sizeof(T));
+    const __amdgpu_buffer_rsrc_t yr = buffer_of(y + (int64_t)item * n_out, n_out * (int)sizeof(T));
+    const int q = q0 + 4 * lane;
+
+    // Columns 4 lane + 256 k .. + 3 of ring t (ring_start in [0, nlon_i)), or
+    // nothing (zeros).  kInside: fp32 tiles away from the seam, four columns
+    // per load; kSeam: the same, the one lane whose columns straddle the seam
+    // taking the ring's last four and first four; kColumns: column by column
+    // (bf16, rings shorter than a slot).
+    auto load_ring = [&](int t, int start, bool on, float4 (&v)[kWalkLoads]) {
+        int base = q0 + start;
+        if (base >= g.nlon_i) base -= g.nlon_i;
+        const int row = t * g.nlon_i;
+#pragma unroll
+        for (int k = 0; k < kWalkLoads; ++k) {
+            const int c = 256 * k + 4 * lane;
+            const bool in = on && c < pitch;
+            if constexpr (LOAD == kInside) {
+                v[k] = buffer_load4(x, xr, in ? row + base + c : -1);
+            } else if constexpr (LOAD == kSeam) {
+                const int i0 = base + c < g.nlon_i ? base + c : base + c - g.nlon_i;
+                const int left = g.nlon_i - i0;  // columns before the seam
+                const bool cut = left < 4;
+                const float4 a = buffer_load4(x, xr, in ? row + (cut ? g.nlon_i - 4 : i0) : -1);
+                const float4 b = buffer_load4(x, xr, in && cut ? row : -1);
+                v[k].x = left >= 4 ? a.x : left == 3 ? a.y : left == 2 ? a.z : a.w;
+                v[k].y = left >= 4 ? a.y : left == 3 ? a.z : left == 2 ? a.w : b.x;
+                v[k].z = left >= 4 ? a.z : left == 3 ? a.w : left == 2 ? b.x : b.y;
+                v[k].w = left >= 4 ? a.w : left == 3 ? b.x : left == 2 ? b.y : b.z;
+            } else {
+                float e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    int idx = base + c + u;
+                    if (idx >= g.nlon_i) idx -= g.nlon_i;
+                    if (g.nlon_i < kWalkMaxPitch) idx %= g.nlon_i;
+                    e[u] = buffer_load1(x, xr, in ? row + idx : -1);
+                }
+                v[k] = make_float4(e[0], e[1], e[2], e[3]);
+            }
+        }
+    };
+    auto put_ring = [&](int slot, bool on, const float4 (&v)[kWalkLoads]) {
+        float4* dst = xs4 + slot * (pitch >> 2) + lane;
+#pragma unroll
+        for (int k = 0; k < kWalkLoads; ++k)
+            if (on && 256 * k + 4 * lane < pitch) {
+                DISCO_CHECK(slot < n_slots && slot * pitch + 256 * k + 4 * lane + 3 < kWalkMaxFloats);
+                dst[64 * k] = v[k];
+            }
+    };
+    // A step's folded weights (n pieces of 64): float4 i of lane l is weights
+    // 256 i + 4 l .. + 3.
+    float* wlds = (float*)(xs4 + n_slots * (pitch >> 2));
+    const __amdgpu_buffer_rsrc_t wr = buffer_of(wc, W.n_weights * 4);
+    auto load_weights = [&](const WStep& S, float4 (&v)[kWalkW4]) {
+#pragma unroll
+        for (int k = 0; k < kWalkW4; ++k) {
+            const int i = 256 * k + 4 * lane;
+            v[k] = buffer_load4(wc, wr, i < 64 * S.n ? 64 * S.piece + i : -1);
+        }
+    };
+    auto put_weights = [&](const float4 (&v)[kWalkW4]) {
+#pragma unroll
+        for (int k = 0; k < kWalkW4; ++k) ((float4*)wlds)[64 * k + lane] = v[k];
+    };
+    WStep S = steps[s0];
+    int slot = S.lo % n_slots;  // the next ring's slot
+    auto advance = [&](bool on) { slot = !on ? slot : slot + 1 < n_slots ? slot + 1 : 0; };
+    {
+        float4 wv[kWalkW4];
+        load_weights(S, wv);
+        for (int t = S.lo; t < S.hi; t += 4) {  // the first window, four rings' loads in flight
+            float4 a[4][kWalkLoads];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load_ring(t + u, ring_start[t + u < S.hi ? t + u : t], t + u < S.hi, a[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                put_ring(slot, t + u < S.hi, a[u]);
+                advance(t + u < S.hi);
+            }
+        }
+        put_weights(wv);
+    }
+    // Step descriptors run two steps ahead of their use, a step's pieces
+    // (lane i holds piece i), weights and new rings one step.
+    WStep N = steps[s0 + 1 < s1 ? s0 + 1 : s0];
+    int desc = pieces[S.piece + (lane < S.n ? lane : 0)];
+    for (int s = s0; s < s1; ++s) {
+        const WStep N2 = steps[s + 2 < s1 ? s + 2 : s1 - 1];
+        const int fresh = N.hi - S.hi;  // rings new to the next step's window
+        const int desc_next = pieces[N.piece + (lane < N.n ? lane : 0)];
+        float4 wv[kWalkW4], pf[kWalkAhead][kWalkLoads];
+        load_weights(N, wv);
+#pragma unroll
+        for (int k = 0; k < kWalkAhead; ++k)
+            load_ring(S.hi + k, ring_start[S.hi + k < g.nlat_i ? S.hi + k : 0], k < fresh, pf[k]);
+        __builtin_amdgcn_wave_barrier();  // the staged columns are written before the reads below
+        v4f acc[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) acc[o] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        walk_pieces(S.n, desc, wlds + lane, xl, acc);
+        // Lane l of a product's column block holds its own output column.
+        if (VEC && g.P == 2) {
+            // The two phases of two output rings, interleaved in memory.
+#pragma unroll
+            for (int r = 0; r < kWalkPats; r += 2) {
+                const int i = q < g.nq && S.pat + r < W.pat_end ? ((S.pat + r) >> 1) * g.nlon_o + 2 * q : -1;
+                const float lo4[4] = {acc[0][r], acc[0][r + 1], acc[1][r], acc[1][r + 1]};
+                const float hi4[4] = {acc[2][r], acc[2][r + 1], acc[3][r], acc[3][r + 1]};
+                buffer_store4(y, yr, i, lo4);
+                buffer_store4(y, yr, i < 0 ? i : i + 4, hi4);
+            }
+        } else if (VEC) {
+#pragma unroll
+            for (int r = 0; r < kWalkPats; ++r) {
+                const float v[4] = {acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+                buffer_store4(y, yr, q < g.nq && S.pat + r < W.pat_end ? (S.pat + r) * g.nlon_o + q : -1, v);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kWalkPats; ++r) {
+                const int pat = S.pat + r, to = pat / g.P, ph = pat - to * g.P;
+#pragma unroll
+                for (int o = 0; o < 4; ++o)
+                    buffer_store1(y, yr, q + o < g.nq && pat < W.pat_end ? to * g.nlon_o + (q + o) * g.P + ph : -1,
+                                  acc[o][r]);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // the step's LDS reads are done before the next rings land
+        put_weights(wv);
+#pragma unroll
+        for (int k = 0; k < kWalkAhead; ++k) {
+            put_ring(slot, k < fresh, pf[k]);
+            advance(k < fresh);
+        }
+        for (int t = S.hi + kWalkAhead; t < N.hi; ++t) {
+            float4 a[kWalkLoads];
+            load_ring(t, ring_start[t], true, a);
+            put_ring(slot, true, a);
+            advance(true);
+        }
+        S = N;
+        N = N2;
+        desc = desc_next;
+    }
+}
+
+// grid: n_runs * n_tiles * items workgroups of 64 threads, dynamic LDS
+// n_slots * pitch + 64 kWalkPieces floats.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(64, 3) void k_stencil_walk(const WStep* __restrict__ steps, const int32_t* __restrict__ pieces,
+                                                     const int32_t* __restrict__ ring_start,
+                                                     const float* __restrict__ fw, WalkArgs W, OpGeom g,
+                                                     const T* __restrict__ x, T* __restrict__ y) {
+    extern __shared__ float4 xs4[];
+    // Work item = (item, run, tile), tiles fastest: the workgroups of one XCD
+    // share rings and halos in its L2.
+    const int bid = xcd_remap(blockIdx.x, gridDim.x);
+    const int item = bid / (W.n_runs * W.n_tiles), rt = bid - item * (W.n_runs * W.n_tiles);
+    const int run = rt / W.n_tiles, q0 = (rt - run * W.n_tiles) * kWalkTile;
+    const int s0 = run * W.run_len, s1 = s0 + W.run_len < W.n_steps ? s0 + W.run_len : W.n_steps;
+    // Away from the seam every ring's columns q0 + lag lie in one turn.
+    if constexpr (sizeof(T) == 4) {
+        if (q0 >= W.back && q0 + W.ahead <= g.nlon_i)
+            return walk_run<T, VEC, kInside>(xs4, steps, pieces, ring_start, fw, W, g, x, y, item, q0, s0, s1);
+        if (g.nlon_i >= kWalkMaxPitch)
+            return walk_run<T, VEC, kSeam>(xs4, steps, pieces, ring_start, fw, W, g, x, y, item, q0, s0, s1);
+    }
+    walk_run<T, VEC, kColumns>(xs4, steps, pieces, ring_start, fw, W, g, x, y, item, q0, s0, s1);
+}
+
+template <typename T>
+hipError_t stencil_walk_launch(const ExecArgs& a, const StencilDev& S, float* fw) {
+    const WalkDev& W = S.walk;
+    const OpGeom& g = a.op->g;
+    const int rows = a.dw_c > 0 ? a.dw_c : 1;
+    int tk = timing_begin("fold_weights", a.stream);
+    hipLaunchKernelGGL(k_fold_weights<T>, dim3((unsigned)((W.n_weights + 255) / 256), (unsigned)rows), dim3(256), 0,
+                       a.stream, W.vals, W.cells, a.op->cmap_dev, (const T*)a.w, fw, W.n_weights,
+                       basis_size(a.op->basis));
+    timing_end(tk, a.stream);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int n_tiles = (g.nq + kWalkTile - 1) / kWalkTile;
+    // Steps per run: long runs stage fewer rings twice, short ones keep more
+    // waves in flight; about 8192 workgroups, 1 to 8 steps each.
+    const int64_t all = (int64_t)W.n_steps * n_tiles * a.B;
+    int run_len = (int)((all + 8191) / 8192);
+    run_len = run_len < 1 ? 1 : run_len > 8 ? 8 : run_len;
+    const int n_runs = (W.n_steps + run_len - 1) / run_len;
+    // Four outputs of a lane in one access: whole lanes, aligned rows.
+    const int align = a.dtype == 1 ? 8 : 16;
+    const bool vec = g.P <= 2 && g.nq % 4 == 0 && g.nlon_o % 4 == 0 && (uintptr_t)a.y % align == 0;
+    const dim3 grid((unsigned)((int64_t)n_runs * n_tiles * a.B));
+    const size_t lds = sizeof(float) * ((size_t)W.n_slots * W.pitch + kWalkPats * kWalkLags * kWalkPieces);
+    const WalkArgs wa{W.n_steps, run_len, n_runs, n_tiles, W.n_slots, W.pitch, W.n_weights, a.dw_c, W.pat_end, W.back, W.ahead};
+    tk = timing_begin("stencil_walk", a.stream);
+    if (vec)
+        hipLaunchKernelGGL((k_stencil_walk<T, true>), grid, dim3(64), lds, a.stream, W.steps, W.pieces,
+                           W.ring_start, (const float*)fw, wa, g, (const T*)a.x, (T*)a.y);
+    else
+        hipLaunchKernelGGL((k_stencil_walk<T, false>), grid, dim3(64), lds, a.stream, W.steps, W.pieces,
+                           W.ring_start, (const float*)fw, wa, g, (const T*)a.x, (T*)a.y);
+    timing_end(tk, a.stream);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t stencil_blocked_parts(const ExecArgs& a, const StencilDev& S, float* ws) {
+    float* partial = (float*)((char*)ws + walk_ws_bytes(a, S));
+    hipError_t e = hipSuccess;
+    if (!(a.walk && a.heavy_spectral))
+        e = S.tile == kStencilSmallTile ? stencil_blocked_launch<T, kStencilSmallTile>(a, S, partial)
+                                        : stencil_blocked_launch<T, kStencilTile>(a, S, partial);
+    if (e != hipSuccess || !a.walk) return e;
+    return stencil_walk_launch<T>(a, S, ws);
 }
 
 }  // namespace
 
 DISCO_BOUNDS_READER(bounds_flag_stencil)
 
-hipError_t launch_stencil_blocked(const ExecArgs& a, const StencilDev& S, float* partial_ws) {
-    if (S.tile == kStencilSmallTile)
-        return a.dtype == 1 ? stencil_blocked_launch<uint16_t, kStencilSmallTile>(a, S, partial_ws)
-                            : stencil_blocked_launch<float, kStencilSmallTile>(a, S, partial_ws);
-    if (S.tile != kStencilTile) return hipErrorInvalidValue;
-    return a.dtype == 1 ? stencil_blocked_launch<uint16_t, kStencilTile>(a, S, partial_ws)
-                        : stencil_blocked_launch<float, kStencilTile>(a, S, partial_ws);
+hipError_t launch_stencil_blocked(const ExecArgs& a, const StencilDev& S, float* ws) {
+    if (S.tile != kStencilSmallTile && S.tile != kStencilTile) return hipErrorInvalidValue;
+    return a.dtype == 1 ? stencil_blocked_parts<uint16_t>(a, S, ws) : stencil_blocked_parts<float>(a, S, ws);
 }
 
 hipError_t launch_stencil(const ExecArgs& a, const PackedDev& P, float* partial_ws) {

@@ -1,0 +1,98 @@
+"""The folded-weight kernels' ring walk and the spectral path of its wide rings
+(one-channel items, stride-1 ops), and the spectral path of ops whose two
+grids have different ring lengths.
+
+A depthwise call of enough items takes the walk and the spectral path; the
+same channel alone is far below that line and, with algo fused_direct, sums
+every ring directly (checked against the fp64 oracle on small grids by the
+other tests).  The two differ by the rounding of sums of up to 128 products
+and of two transforms of at most 512 points in fp32: 2^-24 sqrt(128) and
+2^-24 log2(512) relative to the ring's values, 1e-6 together; bf16 outputs by
+one rounding to 2^-9.
+"""
+import math
+
+import numpy as np
+import pytest
+
+from gpu_util import rel_l2, run_gpu, run_oracle, say, to_numpy, torch_dev
+from paper_2209_13603_amd import disco, synth
+
+pytestmark = pytest.mark.gpu
+
+K = {"bilinear3x3": 9, "axisym4": 4, "separable4x4": 16}
+# (nlat_in, nlon_in, nlat_out, nlon_out, sampling, op, batch, channels): at least 2^21 outputs
+CASES = [
+    (128, 256, 128, 256, "cell_centred", "forward", 1, 64),    # one tile, wrapped both ways
+    (128, 256, 128, 256, "cell_centred", "forward", 3, 23),    # odd channel and batch groups
+    (257, 512, 257, 512, "poles", "forward", 2, 9),            # two tiles, odd ring count
+    (256, 1024, 256, 1024, "cell_centred", "forward", 1, 9),   # tiles away from the seam
+    (128, 256, 64, 128, "cell_centred", "transpose", 2, 35),   # two phases
+    (128, 256, 32, 64, "cell_centred", "transpose", 5, 13),    # four phases
+    (256, 256, 128, 256, "cell_centred", "forward", 1, 65),    # latitude-only change: four new rings a step
+]
+
+
+@pytest.mark.parametrize("basis", list(K))
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dx%d_%dx%d_%s_%s_%dx%d" % c)
+def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis):
+    import torch
+    a, b, c, d, smp, op, B, C = case
+    tc = 3 * math.pi / (min(a, c) - (smp == "poles"))
+    xs = (B, C, a, b) if op == "forward" else (B, C, c, d)
+    x, w = synth.random_inputs(71, xs, (C, K[basis]), dtype=dtype, c_in=1)
+    say("ring walk", case, basis, dtype)
+    plan = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp)
+    one = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp)
+    xt, wt = torch_dev(x, dtype), torch_dev(w, dtype)
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    y = plan.forward_depthwise(xt, wt) if op == "forward" else plan.transpose_depthwise(xt, wt)
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    assert "stencil_walk" in ran and "spectral_mac" in ran
+    for ch in (0, C // 2, C - 1):
+        for bi in (0, B - 1):
+            xc = xt[bi:bi + 1, ch:ch + 1].contiguous()
+            if basis == "bilinear3x3":
+                f = one.forward_depthwise if op == "forward" else one.transpose_depthwise
+                yc = f(xc, wt[ch:ch + 1].contiguous())  # one item: every ring summed directly
+            else:
+                yc, _ = run_gpu(None, to_numpy(xc).astype(np.float32),
+                                to_numpy(wt[ch]).astype(np.float32)[None, None, :], op, dtype=dtype,
+                                algo="fused_direct", plan=one)
+                yc = torch.from_numpy(np.asarray(yc))
+            got, ref = to_numpy(y[bi, ch]), to_numpy(yc)[0, 0]
+            err = rel_l2(got, ref)
+            mx = np.abs(got - ref).max() / np.abs(ref).max()
+            say("  item (%d, %d) rel_l2 %.3e max %.3e" % (bi, ch, err, mx))
+            assert err <= (1e-6 if dtype == "fp32" else 2e-3)
+            assert mx <= (4e-6 if dtype == "fp32" else 8e-3)
+    plan.close()
+    one.close()
+
+
+@pytest.mark.parametrize("op", ["forward", "transpose"])
+@pytest.mark.parametrize("case", [(64, 128, 32, 64), (32, 64, 64, 128), (64, 256, 32, 64), (64, 128, 64, 64)],
+                         ids=lambda c: "%dx%d_%dx%d" % c)
+@pytest.mark.parametrize("chans", [(2, 3), (9, 12)], ids=lambda c: "%dto%d" % c)
+def test_spectral_rings_of_two_lengths(case, op, chans, monkeypatch):
+    """Up- and downsampling by 2 and 4 with most rings on the spectral path,
+    against the oracle in full."""
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "8")
+    a, b, c, d = case
+    args = (a, b, c, d, 3 * math.pi / min(a, c))
+    ci, co = chans
+    xs = (2, ci, a, b) if op == "forward" else (2, ci, c, d)
+    ws = (co, ci, 9) if op == "forward" else (ci, co, 9)
+    x, w = synth.random_inputs(72, xs, ws)
+    say("two ring lengths", case, op, chans)
+    y, plan = run_gpu(args, x, w, op, algo="fused")
+    assert plan.info()["spectral_rings_%s" % op] > 0
+    ref = run_oracle(args, x, w, op)
+    err = rel_l2(y, ref)
+    say("  rel_l2 %.3e" % err)
+    assert err <= 1e-5
+    assert np.abs(y - ref).max() <= 1e-5 * np.abs(ref).max()
+    plan.close()
