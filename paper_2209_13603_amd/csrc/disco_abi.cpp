@@ -330,6 +330,8 @@ disco_status_t upload_walk(const WalkHost& H, StencilDev* d) {
     disco_status_t s;
     WalkDev& W = d->walk;
     if ((s = upload_vec(H.steps, &W.steps, &d->bytes, "hipMalloc(ring-walk steps)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.quads, &W.quads, &d->bytes, "hipMalloc(ring-walk quads)")) != DISCO_OK) return s;
+    if ((s = upload_vec(H.groups, &W.groups, &d->bytes, "hipMalloc(ring-walk groups)")) != DISCO_OK) return s;
     if ((s = upload_vec(H.pieces, &W.pieces, &d->bytes, "hipMalloc(ring-walk pieces)")) != DISCO_OK) return s;
     if ((s = upload_vec(H.ring_start, &W.ring_start, &d->bytes, "hipMalloc(ring-walk rings)")) != DISCO_OK) return s;
     if ((s = upload_vec(H.vals, &W.vals, &d->bytes, "hipMalloc(ring-walk values)")) != DISCO_OK) return s;
@@ -341,12 +343,13 @@ disco_status_t upload_walk(const WalkHost& H, StencilDev* d) {
     W.back = H.back;
     W.ahead = H.ahead;
     W.n_steps = (int32_t)H.steps.size();
+    W.n_groups = (int32_t)H.groups.size();
     return DISCO_OK;
 }
 
 int64_t walk_bytes(const WalkHost& H) {
     if (H.steps.empty()) return 0;
-    return vec_bytes(H.steps) + vec_bytes(H.pieces) + vec_bytes(H.ring_start) + vec_bytes(H.vals) + vec_bytes(H.cells);
+    return vec_bytes(H.steps) + vec_bytes(H.quads) + vec_bytes(H.groups) + vec_bytes(H.pieces) + vec_bytes(H.ring_start) + vec_bytes(H.vals) + vec_bytes(H.cells);
 }
 
 int64_t stencil_bytes(const StencilHost& H) {
@@ -610,7 +613,7 @@ void free_op(DeviceOp* d) {
     d->mfma_state = 0;
     const WalkDev& W = d->stencil.walk;
     void* sp[] = {d->stencil.pieces, d->stencil.chunks, d->stencil.vals, d->stencil.cells,
-                  W.steps, W.pieces, W.ring_start, W.vals, W.cells};
+                  W.steps, W.quads, W.groups, W.pieces, W.ring_start, W.vals, W.cells};
     for (void* p : sp)
         if (p) (void)hipFree(p);
     free_packed(&d->stencil.P);
@@ -1204,6 +1207,25 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
         return ez == hipSuccess ? ok() : hip_fail(ez, "kernel launch");
     }
     struct Restore { int d; bool on; ~Restore() { if (on) (void)hipSetDevice(d); } } restore{cur, cur != plan->device};
+    // One-channel items (depthwise calls, a single channel of the other
+    // bases): correlations of dy and x instead of gathered sums, where the
+    // op's rings are covered by the walk and the spectral tables.
+    const bool folded = (depthwise || (op.basis != DISCO_BASIS_BILINEAR_3X3 && C_x == 1 && C_dy == 1)) && op.has_walk &&
+                        (op.n_entries_wide == 0 || op.n_heavy_rings > 0);
+    if (folded) {
+        const int parts = kPartStencil | (op.n_heavy_rings > 0 ? kPartCore : 0);
+        if ((s = ensure_parts(plan, op, parts)) != DISCO_OK) return s;
+        ExecArgs fa{};
+        fa.op = &op; fa.x = x->data; fa.dy = dy->data; fa.dw = dw->data; fa.dtype = x->dtype;
+        fa.B = (int)(B * C_x); fa.Ci = fa.Co = 1; fa.dw_c = (int)C_x; fa.stream = ds; fa.walk = true;
+        const size_t need = fold_grad_plan(fa, op.stencil).total();
+        void* ws = nullptr;
+        hipError_t e = hipMallocAsync(&ws, need, ds);
+        if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(weight gradient workspace)");
+        e = launch_stencil_blocked(fa, op.stencil, (float*)ws);
+        (void)hipFreeAsync(ws, ds);
+        return e == hipSuccess ? ok() : hip_fail(e, "kernel launch");
+    }
     // fp32 with the 3x3 basis: Z of all channels in one pass (sweep Z mode,
     // spectral rings' products without the contraction); otherwise the op's own kernels
     // once per input channel (items of B * C_x).

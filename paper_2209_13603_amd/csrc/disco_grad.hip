@@ -370,6 +370,19 @@ hipError_t launch_weight_grad_dw(const void* dy, const void* zs, void* dw, float
     return weight_grad_dw<float>((const float*)dy, (const float*)zs, (float*)dw, ws, B, C, K, P, s);
 }
 
+hipError_t launch_weight_grad_reduce_dw(const float* partial, void* dw, int dtype, int C, int chunks, int K,
+                                        hipStream_t s) {
+    const int tk = timing_begin("weight_grad_reduce", s);
+    if (dtype == 1)
+        hipLaunchKernelGGL((k_weight_grad_reduce_dw<uint16_t>), dim3((unsigned)(C * K)), dim3(kBlock), 0, s, partial,
+                           (uint16_t*)dw, 1, C, chunks, K);
+    else
+        hipLaunchKernelGGL((k_weight_grad_reduce_dw<float>), dim3((unsigned)(C * K)), dim3(kBlock), 0, s, partial,
+                           (float*)dw, 1, C, chunks, K);
+    timing_end(tk, s);
+    return hipGetLastError();
+}
+
 size_t weight_grad_ws_bytes(int B, int M, int N, int64_t P) {
     return sizeof(float) * (size_t)wg_slabs(B, M, N, P) * (size_t)M * (size_t)N;
 }

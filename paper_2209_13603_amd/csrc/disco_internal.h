@@ -244,8 +244,16 @@ struct WStep {
     int32_t pad[3];
 };
 static_assert(sizeof(WStep) == 32, "WStep layout");
+// Weight gradient over the same layout (k_walk_grad): a group is up to
+// kWalkQuads runs of four lags of one step's pieces, whose sums over pixels
+// one wave accumulates in registers.
+constexpr int kWalkQuads = 28;
+struct WQuad { int32_t col, w; };               // first column for output 0; first weight
+struct WGroup { int32_t step, quad, n, pad; };  // quads [quad, quad + n)
 struct WalkHost {
     std::vector<WStep> steps;
+    std::vector<WQuad> quads;
+    std::vector<WGroup> groups;
     std::vector<int32_t> pieces;
     std::vector<int32_t> ring_start;  // per input ring: lag of column 0, mod nlon_i
     std::vector<PVal> vals;           // per piece [kWalkLags][kWalkPats]: the entry's cell's values times q, or zeros
@@ -260,11 +268,13 @@ int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out,
 
 struct WalkDev {
     WStep* steps = nullptr;
+    WQuad* quads = nullptr;
+    WGroup* groups = nullptr;
     int32_t* pieces = nullptr;
     int32_t* ring_start = nullptr;
     PVal* vals = nullptr;
     uint8_t* cells = nullptr;
-    int32_t n_steps = 0, n_weights = 0, pat_end = 0, n_slots = 0, pitch = 0, back = 0, ahead = 0;
+    int32_t n_steps = 0, n_groups = 0, n_weights = 0, pat_end = 0, n_slots = 0, pitch = 0, back = 0, ahead = 0;
 };
 
 // ---------------------------------------------------------------------------
@@ -549,6 +559,10 @@ struct ExecArgs {
     // patterns through k_stencil_walk, the others through the blocked kernel
     // (heavy_spectral: the spectral path writes those instead).
     bool walk = false, heavy_spectral = false;
+    // Weight gradient of one-channel items instead (launch_stencil_blocked):
+    // the upstream gradient, laid out as y, and dW [dw_c or 1][K].
+    const void* dy = nullptr;
+    void* dw = nullptr;
 };
 
 // The plan's device (the one that created it).
@@ -638,6 +652,45 @@ inline size_t stencil_ws_bytes(const ExecArgs& a, const StencilDev& S) {
     const bool partials = !(a.walk && a.heavy_spectral);
     return walk_ws_bytes(a, S) + (partials ? sizeof(float) * (size_t)S.P.n_slots * a.B * a.op->g.nq : 0);
 }
+// The weight gradient of one-channel items (a.dw set; the op has a ring
+// walk, and spectral tables for its wide rings if it has any): with W folded
+// into psi, dW[c][k] = sum over entries of psi_k times the correlation of dy
+// and x at the entry's rings and lag, so one product per stored entry and
+// pixel instead of a gathered sum per basis function.  Workspace: the
+// correlations of the narrow rings [split][channel][weight], the transforms
+// of x and dy on the wide ones, partial sums of dW [channel][chunk][K].
+constexpr int kFoldGradChunks = 32;    // partial sums per channel of the narrow rings' contraction
+constexpr int kFoldGradSegments = 8;   // ... of each wide ring, over its bins
+struct FoldGradPlan {
+    int splits = 1, chunks = 0;
+    size_t corr = 0, xhat = 0, dyhat = 0, partial = 0;  // bytes
+    size_t total() const { return corr + xhat + dyhat + partial; }
+};
+inline FoldGradPlan fold_grad_plan(const ExecArgs& a, const StencilDev& S) {
+    FoldGradPlan p;
+    const int64_t C = a.dw_c > 0 ? a.dw_c : 1, K = basis_size(a.op->basis);
+    const int64_t n_tiles = (a.op->g.nq + kWalkTile - 1) / kWalkTile, most = n_tiles * (a.B / C);
+    // About 4096 waves: the (batch item, tile) sums of a group are split
+    // between waves when there are few groups and channels.
+    int64_t splits = (4096 + S.walk.n_groups * C - 1) / (S.walk.n_groups * C);
+    splits = splits < 1 ? 1 : splits > most ? most : splits;
+    p.splits = (int)(splits < 1 ? 1 : splits);
+    const SpectralDev& D = a.op->spectral;
+    const int64_t H = a.op->n_heavy_rings > 0 ? D.n_rings : 0;
+    p.chunks = kFoldGradChunks + (int)(H * kFoldGradSegments);
+    auto up = [](int64_t n) { return ((size_t)n + 255) / 256 * 256; };
+    p.corr = up(4 * p.splits * C * S.walk.n_weights);
+    p.xhat = H > 0 ? up(8 * (int64_t)D.n_slots * a.B * (D.Mi + 1)) : 0;
+    p.dyhat = up(8 * H * a.B * (D.Mo + 1));
+    p.partial = up(4 * C * p.chunks * K);
+    return p;
+}
+// The wide rings' part (disco_spectral.hip): partial sums of chunks
+// [kFoldGradChunks, chunks) from the transforms of a.x and a.dy.
+hipError_t launch_spectral_fold_grad(const ExecArgs& a, float2* xh, float2* dyh, float* partial, int chunks);
+// dW [C][K] from partial sums [C][chunks][K], in chunk order (disco_grad.hip).
+hipError_t launch_weight_grad_reduce_dw(const float* partial, void* dw, int dtype, int C, int chunks, int K,
+                                        hipStream_t s);
 hipError_t launch_stencil_blocked(const ExecArgs& a, const StencilDev& S, float* partial_ws);
 
 // Weight gradient reduction (disco_grad.hip): G[m][n] = sum_{b,p} A[b][m][p]

@@ -673,6 +673,13 @@ int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out,
         H.cells.resize(H.vals.size(), 0);
         for (const Piece2& b : pc) {
             H.pieces.push_back(walk_piece(b.ti % H.n_slots * H.pitch + b.col, b.lags));
+            for (int q = 0; 4 * q < b.lags; ++q) {
+                if (H.groups.empty() || H.groups.back().step != (int32_t)s || H.groups.back().n == kWalkQuads)
+                    H.groups.push_back(WGroup{(int32_t)s, (int32_t)H.quads.size(), 0, 0});
+                ++H.groups.back().n;
+                H.quads.push_back(WQuad{b.ti % H.n_slots * H.pitch + b.col + 4 * q,
+                                        (int32_t)((H.pieces.size() - 1) * kWalkLags + 4 * q) * kWalkPats});
+            }
             if (b.col + (b.lags + 3 + 3) / 4 * 4 + kWalkTile - 4 > H.pitch) {
                 if (err) *err = "internal: ring-walk columns past the slot";
                 return DISCO_ERR_DEVICE;

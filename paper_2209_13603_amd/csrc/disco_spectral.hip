@@ -414,12 +414,18 @@ template <> struct FoldRows<DISCO_BASIS_BILINEAR_3X3> {
         const int a = 3 * (r / 3);
         return r % 3 == 0 ? w(a) + w(a + 2) : r % 3 == 1 ? w(a + 2) - w(a) : w(a + 1);
     }
+    // Basis function k's sum from the rows' sums (conj(Vhat_3a) against Q, then Vhat_3a).
+    static __device__ float basis(const float (&g)[K], int k) {
+        const int a = 3 * (k / 3);
+        return k % 3 == 0 ? g[a] + g[a + 1] : k % 3 == 2 ? g[a] - g[a + 1] : g[a + 2];
+    }
 };
 template <> struct FoldRows<DISCO_BASIS_AXISYMMETRIC_4> {
     static constexpr int K = 4;
     static constexpr bool imag(int) { return false; }
     static constexpr int mirror(int r) { return r; }
     template <class W> static __device__ float weight(W w, int r) { return w(r); }
+    static __device__ float basis(const float (&g)[K], int k) { return g[k]; }
 };
 template <> struct FoldRows<DISCO_BASIS_SEPARABLE_4X4> {
     static constexpr int K = 16;
@@ -428,6 +434,10 @@ template <> struct FoldRows<DISCO_BASIS_SEPARABLE_4X4> {
     template <class W> static __device__ float weight(W w, int r) {
         const int a = r & ~3;
         return r % 4 == 0 ? w(a) : r % 4 == 1 ? w(a + 1) + w(a + 3) : r % 4 == 2 ? w(a + 3) - w(a + 1) : w(a + 2);
+    }
+    static __device__ float basis(const float (&g)[K], int k) {
+        const int a = k & ~3;
+        return k % 4 == 0 ? g[a] : k % 4 == 2 ? g[a + 3] : k % 4 == 1 ? g[a + 1] + g[a + 2] : g[a + 1] - g[a + 2];
     }
 };
 
@@ -516,6 +526,84 @@ __global__ __launch_bounds__(64) void k_spectral_fold(const int32_t* __restrict_
         for (int bt = 0; bt < BT; ++bt)
             if (c0 + ct < C && b0 + bt < B)
                 yh[((int64_t)h * B * C + (b0 + bt) * C + c0 + ct) * ystride + m] = Y[ct][bt];
+}
+
+// The weight gradient's share of ring h: with Q = sum_b Xhat conj(DYhat) of a
+// (pair, bin), dW_k gains Re(Q conj(Vhat_k)), so each table row is summed
+// against Re Q, or Im Q for imaginary parts, and the rows of one conjugate
+// pair of basis functions are combined at the end.  DYhat: the real DFT of dy
+// on the op's rings, interior bins doubled (Parseval).  A wave takes every
+// kFoldGradSegments-th block of 64 bins of one ring for CT channels.
+// partial: [C][chunks][K], chunk kFoldGradChunks + h kFoldGradSegments + segment.
+// grid: kFoldGradSegments * n_rings * ceil(C / CT) (spec_item)
+template <int BASIS, int CT, bool GEO>
+__global__ __launch_bounds__(64) void k_spectral_fold_grad(const int32_t* __restrict__ pair_ptr,
+                                                           const int32_t* __restrict__ pair_slot,
+                                                           const int32_t* __restrict__ pair_tab,
+                                                           const float* __restrict__ vs,
+                                                           const float2* __restrict__ xh,
+                                                           const float2* __restrict__ dyh, float* __restrict__ partial,
+                                                           int B, int C, int chunks, SpecGeom S, int n_rings) {
+    using R = FoldRows<BASIS>;
+    constexpr int K = R::K;
+    const int lane = threadIdx.x, nct = (C + CT - 1) / CT;
+    int seg, h, iz;
+    spec_item(kFoldGradSegments, n_rings, nct, &seg, &h, &iz);
+    const int c0 = iz * CT;
+    const int64_t vstride = (int64_t)(S.M + 1), xstride = (int64_t)(S.Mi + 1), ystride = (int64_t)(S.Mo + 1);
+    float G[CT][K];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < K; ++r) G[ct][r] = 0.0f;
+    for (int ix = seg; 64 * ix <= S.Mo; ix += kFoldGradSegments) {
+        const int mo = 64 * ix + lane, m = mo < S.Mo ? mo : S.Mo;
+        const float on = mo <= S.Mo ? 1.0f : 0.0f;
+        for (int p = pair_ptr[h]; p < pair_ptr[h + 1]; ++p) {
+            const int32_t tb = pair_tab[p];
+            const float* vt = vs + (int64_t)(tb & 0x7fffffff) * K * vstride;
+            const float2* xp = xh + (int64_t)pair_slot[p] * B * C * xstride;
+            const float2* dp = dyh + (int64_t)h * B * C * ystride + m;
+            for (int al = 0; al < (GEO ? S.alias : 1); ++al) {
+                int mv = m, mx = m;
+                float sv = 1.0f, sx = 1.0f;
+                if constexpr (GEO) spec_bins(S, m, al, &mv, &mx, &sv, &sx);
+                float V[K];
+#pragma unroll
+                for (int r = 0; r < K; ++r) V[r] = on * vt[(tb < 0 ? R::mirror(r) : r) * vstride + mv];
+                float qr[CT], qi[CT];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) qr[ct] = qi[ct] = 0.0f;
+                for (int b = 0; b < B; ++b)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        const int64_t item = (int64_t)b * C + (c0 + ct < C ? c0 + ct : C - 1);
+                        const float2 X = xp[item * xstride + mx], D = dp[item * ystride];
+                        const float xy = GEO ? sx * X.y : X.y;
+                        qr[ct] = fmaf(X.x, D.x, fmaf(xy, D.y, qr[ct]));
+                        qi[ct] = fmaf(xy, D.x, fmaf(-X.x, D.y, qi[ct]));
+                    }
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    if constexpr (GEO) qi[ct] *= sv;
+#pragma unroll
+                    for (int r = 0; r < K; ++r) G[ct][r] = fmaf(V[r], R::imag(r) ? qi[ct] : qr[ct], G[ct][r]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) G[ct][r] += __shfl_xor(G[ct][r], off, 64);
+        if (lane == 0 && c0 + ct < C) {
+            float* out = partial + ((int64_t)(c0 + ct) * chunks + kFoldGradChunks + h * kFoldGradSegments + seg) * K;
+#pragma unroll
+            for (int k = 0; k < K; ++k) out[k] = R::basis(G[ct], k);
+        }
+    }
 }
 
 // y[b][co][ring][:] = inverse real DFT of Yhat[h][b][co][:].  grid: (n_rings, B * Co)
@@ -709,6 +797,54 @@ hipError_t launch_spectral_dyhat(const ExecArgs& a, const float* dy, int C, floa
                        S.rings, dy, (const float2*)S.tw, dyh, a.B, C, a.op->g.nlat_o, S.Mo, S.M / S.Mo, 2.0f);
     timing_end(tk, a.stream);
     return hipGetLastError();
+}
+
+namespace {
+
+template <int BASIS>
+void spectral_fold_grad(const ExecArgs& a, const float2* xh, const float2* dyh, float* partial, int chunks) {
+    const SpectralDev& S = a.op->spectral;
+    const SpecGeom G = spec_geom(a);
+    constexpr int CT = 4;
+    const int C = a.dw_c > 0 ? a.dw_c : 1, B = a.B / C;
+    const dim3 grid((unsigned)((int64_t)kFoldGradSegments * S.n_rings * ((C + CT - 1) / CT)));
+    if (same_rings(G))
+        hipLaunchKernelGGL((k_spectral_fold_grad<BASIS, CT, false>), grid, dim3(64), 0, a.stream, S.pair_ptr,
+                           S.pair_slot, S.pair_tab, S.vs, xh, dyh, partial, B, C, chunks, G, S.n_rings);
+    else
+        hipLaunchKernelGGL((k_spectral_fold_grad<BASIS, CT, true>), grid, dim3(64), 0, a.stream, S.pair_ptr,
+                           S.pair_slot, S.pair_tab, S.vs, xh, dyh, partial, B, C, chunks, G, S.n_rings);
+}
+
+template <typename T>
+hipError_t spectral_fold_grad_all(const ExecArgs& a, float2* xh, float2* dyh, float* partial, int chunks) {
+    const SpectralDev& S = a.op->spectral;
+    hipError_t e = spectral_rfft<T>(a, xh);
+    if (e != hipSuccess) return e;
+    int tk = timing_begin("spectral_rfft_dy", a.stream);
+    hipLaunchKernelGGL((k_rfft_rings<T>), dim3(S.n_rings, a.B), dim3(kFftBlock), fft_lds_bytes(S.Mo), a.stream, S.rings,
+                       (const T*)a.dy, (const float2*)S.tw, dyh, a.B, 1, a.op->g.nlat_o, S.Mo, S.M / S.Mo, 2.0f);
+    timing_end(tk, a.stream);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    tk = timing_begin("spectral_grad", a.stream);
+    switch (a.op->basis) {
+        case DISCO_BASIS_AXISYMMETRIC_4:
+            spectral_fold_grad<DISCO_BASIS_AXISYMMETRIC_4>(a, xh, dyh, partial, chunks);
+            break;
+        case DISCO_BASIS_SEPARABLE_4X4:
+            spectral_fold_grad<DISCO_BASIS_SEPARABLE_4X4>(a, xh, dyh, partial, chunks);
+            break;
+        default: spectral_fold_grad<DISCO_BASIS_BILINEAR_3X3>(a, xh, dyh, partial, chunks);
+    }
+    timing_end(tk, a.stream);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_spectral_fold_grad(const ExecArgs& a, float2* xh, float2* dyh, float* partial, int chunks) {
+    return a.dtype == 1 ? spectral_fold_grad_all<uint16_t>(a, xh, dyh, partial, chunks)
+                        : spectral_fold_grad_all<float>(a, xh, dyh, partial, chunks);
 }
 
 hipError_t launch_spectral(const ExecArgs& a, float* ws, int stages) {

@@ -491,6 +491,50 @@ constexpr int kWalkAhead = 4;                            // rings staged one ste
 constexpr int kWalkW4 = kWalkPieces * kWalkPats * kWalkLags / 256;  // float4 weights per lane of a step
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+enum { kColumns = 0, kInside = 1, kSeam = 2 };  // how a tile's columns are loaded
+
+// Columns 4 lane + 256 k .. + 3 of ring t for the tile at q0 (start: the
+// ring's ring_start), or nothing (zeros).  kInside: fp32 tiles away from the
+// seam, four columns per load; kSeam: the same, the one lane whose columns
+// straddle the seam taking the ring's last four and first four; kColumns:
+// column by column (bf16, rings shorter than a slot).
+template <typename T, int LOAD>
+__device__ __forceinline__ void walk_load_ring(const T* __restrict__ x, __amdgpu_buffer_rsrc_t xr, const OpGeom& g,
+                                               int q0, int t, int start, bool on, int pitch,
+                                               float4 (&v)[kWalkLoads]) {
+    int base = q0 + start;
+    if (base >= g.nlon_i) base -= g.nlon_i;
+    const int row = t * g.nlon_i;
+#pragma unroll
+    for (int k = 0; k < kWalkLoads; ++k) {
+        const int c = 256 * k + 4 * (int)threadIdx.x;
+        const bool in = on && c < pitch;
+        if constexpr (LOAD == kInside) {
+            v[k] = buffer_load4(x, xr, in ? row + base + c : -1);
+        } else if constexpr (LOAD == kSeam) {
+            const int i0 = base + c < g.nlon_i ? base + c : base + c - g.nlon_i;
+            const int left = g.nlon_i - i0;  // columns before the seam
+            const bool cut = left < 4;
+            const float4 a = buffer_load4(x, xr, in ? row + (cut ? g.nlon_i - 4 : i0) : -1);
+            const float4 b = buffer_load4(x, xr, in && cut ? row : -1);
+            v[k].x = left >= 4 ? a.x : left == 3 ? a.y : left == 2 ? a.z : a.w;
+            v[k].y = left >= 4 ? a.y : left == 3 ? a.z : left == 2 ? a.w : b.x;
+            v[k].z = left >= 4 ? a.z : left == 3 ? a.w : left == 2 ? b.x : b.y;
+            v[k].w = left >= 4 ? a.w : left == 3 ? b.x : left == 2 ? b.y : b.z;
+        } else {
+            float e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                int idx = base + c + u;
+                if (idx >= g.nlon_i) idx -= g.nlon_i;
+                if (g.nlon_i < kWalkMaxPitch) idx %= g.nlon_i;
+                e[u] = buffer_load1(x, xr, in ? row + idx : -1);
+            }
+            v[k] = make_float4(e[0], e[1], e[2], e[3]);
+        }
+    }
+}
+
 // One piece in registers: the lane's columns from the piece's first one on,
 // and the folded weights as A operand (lane i + 4 b: pattern i, lag b).
 struct WalkPiece {
@@ -565,7 +609,6 @@ struct WalkArgs {
 // cores, four patterns by 64 outputs per instruction; as VALU FMAs the
 // weights would be scalar operands, at which the FMA rate halves.  VEC: four
 // outputs per store (P <= 2, whole lanes, aligned rows).
-enum { kColumns = 0, kInside = 1, kSeam = 2 };  // how a tile's columns are loaded
 template <typename T, bool VEC, int LOAD>
 __device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* __restrict__ steps,
                                          const int32_t* __restrict__ pieces, const int32_t* __restrict__ ring_start,
@@ -580,43 +623,8 @@ __device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* 
     const __amdgpu_buffer_rsrc_t yr = buffer_of(y + (int64_t)item * n_out, n_out * (int)sizeof(T));
     const int q = q0 + 4 * lane;
 
-    // Columns 4 lane + 256 k .. + 3 of ring t (ring_start in [0, nlon_i)), or
-    // nothing (zeros).  kInside: fp32 tiles away from the seam, four columns
-    // per load; kSeam: the same, the one lane whose columns straddle the seam
-    // taking the ring's last four and first four; kColumns: column by column
-    // (bf16, rings shorter than a slot).
     auto load_ring = [&](int t, int start, bool on, float4 (&v)[kWalkLoads]) {
-        int base = q0 + start;
-        if (base >= g.nlon_i) base -= g.nlon_i;
-        const int row = t * g.nlon_i;
-#pragma unroll
-        for (int k = 0; k < kWalkLoads; ++k) {
-            const int c = 256 * k + 4 * lane;
-            const bool in = on && c < pitch;
-            if constexpr (LOAD == kInside) {
-                v[k] = buffer_load4(x, xr, in ? row + base + c : -1);
-            } else if constexpr (LOAD == kSeam) {
-                const int i0 = base + c < g.nlon_i ? base + c : base + c - g.nlon_i;
-                const int left = g.nlon_i - i0;  // columns before the seam
-                const bool cut = left < 4;
-                const float4 a = buffer_load4(x, xr, in ? row + (cut ? g.nlon_i - 4 : i0) : -1);
-                const float4 b = buffer_load4(x, xr, in && cut ? row : -1);
-                v[k].x = left >= 4 ? a.x : left == 3 ? a.y : left == 2 ? a.z : a.w;
-                v[k].y = left >= 4 ? a.y : left == 3 ? a.z : left == 2 ? a.w : b.x;
-                v[k].z = left >= 4 ? a.z : left == 3 ? a.w : left == 2 ? b.x : b.y;
-                v[k].w = left >= 4 ? a.w : left == 3 ? b.x : left == 2 ? b.y : b.z;
-            } else {
-                float e[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    int idx = base + c + u;
-                    if (idx >= g.nlon_i) idx -= g.nlon_i;
-                    if (g.nlon_i < kWalkMaxPitch) idx %= g.nlon_i;
-                    e[u] = buffer_load1(x, xr, in ? row + idx : -1);
-                }
-                v[k] = make_float4(e[0], e[1], e[2], e[3]);
-            }
-        }
+        walk_load_ring<T, LOAD>(x, xr, g, q0, t, start, on, pitch, v);
     };
     auto put_ring = [&](int slot, bool on, const float4 (&v)[kWalkLoads]) {
         float4* dst = xs4 + slot * (pitch >> 2) + lane;
@@ -784,6 +792,175 @@ hipError_t stencil_walk_launch(const ExecArgs& a, const StencilDev& S, float* fw
     return hipGetLastError();
 }
 
+// The correlations of dy and x over the ring walk's layout (Sec. 4.2, the
+// adjoint of the folded product): corr[split][c][w] = sum over the split's
+// batch items and tiles and the outputs q of dy[pattern][q] x[ring][q + lag]
+// for every weight w = (piece, lag, pattern) of a group.  One wave per
+// (group, channel, split): per tile it stages the step's rings and holds 16
+// dy operands (lane i + 4 b: pattern i, output 16 t + b), and one
+// v_mfma_f32_4x4x1_16b_f32 takes four patterns by four lags at 16 outputs; the
+// sixteen blocks' sums stay in registers until the end.  Per product one LDS
+// read of 64 floats, which with the matrix cores bounds it.
+// grid: splits * C * n_groups workgroups of 64, dynamic LDS n_slots * pitch floats.
+template <typename T, int LOAD>
+__global__ __launch_bounds__(64, 2) void k_walk_grad(const WGroup* __restrict__ groups, const WQuad* __restrict__ quads,
+                                                     const WStep* __restrict__ steps,
+                                                     const int32_t* __restrict__ ring_start, WalkArgs W, OpGeom g,
+                                                     const T* __restrict__ x, const T* __restrict__ dy,
+                                                     float* __restrict__ corr, int n_groups, int B, int C, int splits) {
+    extern __shared__ float4 xs4[];
+    const float* xs = (const float*)xs4;
+    const int lane = threadIdx.x, pitch = W.pitch, n_slots = W.n_slots;
+    // Work item = (channel, split, group), groups fastest.
+    const int bid = xcd_remap(blockIdx.x, gridDim.x);
+    const int grp = bid % n_groups, cs = bid / n_groups;
+    const int split = cs % splits, c = cs / splits;
+    const WGroup G = groups[grp];
+    const WStep S = steps[G.step];
+    const WQuad mine = quads[G.quad + (lane < G.n ? lane : 0)];  // lane i holds quad i
+    const int n_in = g.nlat_i * g.nlon_i, n_out = g.nlat_o * g.nlon_o;
+    // This lane's pattern of dy and column of a product.
+    const int pat = S.pat + (lane & 3), to = pat / g.P, ph = pat - to * g.P;
+    const bool pat_on = pat < W.pat_end;
+    const int xcol = (lane >> 2) + (lane & 3);
+    v4f acc[kWalkQuads];
+#pragma unroll
+    for (int k = 0; k < kWalkQuads; ++k) acc[k] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int u = split; u < B * W.n_tiles; u += splits) {
+        const int b = u / W.n_tiles, q0 = (u - b * W.n_tiles) * kWalkTile;
+        const __amdgpu_buffer_rsrc_t xr = buffer_of(x + ((int64_t)b * C + c) * n_in, n_in * (int)sizeof(T));
+        const __amdgpu_buffer_rsrc_t dr = buffer_of(dy + ((int64_t)b * C + c) * n_out, n_out * (int)sizeof(T));
+        float A[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const int q = q0 + 16 * t + (lane >> 2);
+            A[t] = buffer_load1(dy, dr, pat_on && q < g.nq ? to * g.nlon_o + q * g.P + ph : -1);
+        }
+        int slot = S.lo % n_slots;
+        __builtin_amdgcn_wave_barrier();  // the previous tile's reads are done
+        for (int t = S.lo; t < S.hi; t += 4) {
+            float4 v[4][kWalkLoads];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                walk_load_ring<T, LOAD>(x, xr, g, q0, t + k, ring_start[t + k < S.hi ? t + k : t], t + k < S.hi, pitch,
+                                        v[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (t + k < S.hi) {
+#pragma unroll
+                    for (int l = 0; l < kWalkLoads; ++l)
+                        if (256 * l + 4 * lane < pitch) xs4[slot * (pitch >> 2) + 64 * l + lane] = v[k][l];
+                    slot = slot + 1 < n_slots ? slot + 1 : 0;
+                }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < kWalkQuads; ++k) {
+            if (k >= G.n) continue;  // the same for every lane
+            const int col = __builtin_amdgcn_readlane(mine.col, k) + xcol;
+            DISCO_CHECK(col >= 0 && col + 240 < n_slots * pitch);
+#pragma unroll
+            for (int t = 0; t < 16; ++t)
+                acc[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[t], xs[col + 16 * t], acc[k], 0, 0, 0);
+        }
+    }
+    // Lane j + 4 b holds block b's sums for lag j, patterns 0..3.
+    float* out = corr + ((int64_t)split * C + c) * W.n_weights;
+#pragma unroll
+    for (int k = 0; k < kWalkQuads; ++k) {
+        if (k >= G.n) continue;
+        v4f v = acc[k];
+#pragma unroll
+        for (int off = 4; off < 64; off <<= 1)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] += __shfl_xor(v[r], off, 64);
+        const int w = __builtin_amdgcn_readlane(mine.w, k);
+        if (lane < 4) *(v4f*)(out + w + 4 * lane) = v;
+    }
+}
+
+// partial[c][chunk][k] = sum over the chunk's weights of psi_k times their
+// correlation (summed over splits).  Weights without an entry are left out,
+// whatever their correlation holds.  grid: (kFoldGradChunks, C)
+__global__ __launch_bounds__(256) void k_walk_grad_contract(const PVal* __restrict__ vals,
+                                                            const uint8_t* __restrict__ cells,
+                                                            const int8_t* __restrict__ cmap,
+                                                            const float* __restrict__ corr, float* __restrict__ partial,
+                                                            int n, int C, int splits, int chunks, int K) {
+    __shared__ float red[4][kSeparableBasis];
+    __shared__ int map[kCells];
+    const int c = blockIdx.y, tid = threadIdx.x;
+    if (tid < kCells) {  // four basis functions per cell, a byte each
+        int m = 0;
+        for (int j = 0; j < 4; ++j) m |= (cmap[4 * tid + j] & 255) << (8 * j);
+        map[tid] = m;
+    }
+    __syncthreads();
+    float acc[kSeparableBasis];
+#pragma unroll
+    for (int k = 0; k < kSeparableBasis; ++k) acc[k] = 0.0f;
+    for (int i = blockIdx.x * 256 + tid; i < n; i += kFoldGradChunks * 256) {
+        const PVal v = vals[i];
+        if (v.v[0] == 0.0f && v.v[1] == 0.0f && v.v[2] == 0.0f && v.v[3] == 0.0f) continue;
+        float s = 0.0f;
+        for (int sp = 0; sp < splits; ++sp) s += corr[((int64_t)sp * C + c) * n + i];
+        const int m = map[cells[i]];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int kj = (m >> (8 * j)) & 255;
+            const float p = v.v[j] * s;
+#pragma unroll
+            for (int k = 0; k < kSeparableBasis; ++k) acc[k] += kj == k ? p : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kSeparableBasis; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
+        if ((tid & 63) == 0) red[tid >> 6][k] = acc[k];
+    }
+    __syncthreads();
+    if (tid < K)
+        partial[((int64_t)c * chunks + blockIdx.x) * K + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+}
+
+template <typename T>
+hipError_t fold_grad(const ExecArgs& a, const StencilDev& S, float* ws) {
+    const WalkDev& W = S.walk;
+    const OpGeom& g = a.op->g;
+    const FoldGradPlan F = fold_grad_plan(a, S);
+    float* corr = ws;
+    float2* xh = (float2*)((char*)ws + F.corr);
+    float2* dyh = (float2*)((char*)xh + F.xhat);
+    float* partial = (float*)((char*)dyh + F.dyhat);
+    const int C = a.dw_c > 0 ? a.dw_c : 1, B = a.B / C, K = basis_size(a.op->basis);
+    const int n_tiles = (g.nq + kWalkTile - 1) / kWalkTile;
+    hipError_t e = a.op->n_heavy_rings > 0 ? launch_spectral_fold_grad(a, xh, dyh, partial, F.chunks) : hipSuccess;
+    if (e != hipSuccess) return e;
+    const WalkArgs wa{W.n_steps, 0, 0, n_tiles, W.n_slots, W.pitch, W.n_weights, a.dw_c, W.pat_end, W.back, W.ahead};
+    const dim3 grid((unsigned)((int64_t)F.splits * C * W.n_groups));
+    const size_t lds = sizeof(float) * (size_t)W.n_slots * W.pitch;
+    int tk = timing_begin("walk_grad", a.stream);
+    bool done = false;
+    if constexpr (sizeof(T) == 4)
+        if (g.nlon_i >= kWalkMaxPitch) {
+            hipLaunchKernelGGL((k_walk_grad<T, kSeam>), grid, dim3(64), lds, a.stream, W.groups, W.quads, W.steps,
+                               W.ring_start, wa, g, (const T*)a.x, (const T*)a.dy, corr, W.n_groups, B, C, F.splits);
+            done = true;
+        }
+    if (!done)
+        hipLaunchKernelGGL((k_walk_grad<T, kColumns>), grid, dim3(64), lds, a.stream, W.groups, W.quads, W.steps,
+                           W.ring_start, wa, g, (const T*)a.x, (const T*)a.dy, corr, W.n_groups, B, C, F.splits);
+    timing_end(tk, a.stream);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    tk = timing_begin("walk_grad_contract", a.stream);
+    hipLaunchKernelGGL(k_walk_grad_contract, dim3(kFoldGradChunks, C), dim3(256), 0, a.stream, W.vals, W.cells,
+                       a.op->cmap_dev, corr, partial, W.n_weights, C, F.splits, F.chunks, K);
+    timing_end(tk, a.stream);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return launch_weight_grad_reduce_dw(partial, a.dw, a.dtype, C, F.chunks, K, a.stream);
+}
+
 template <typename T>
 hipError_t stencil_blocked_parts(const ExecArgs& a, const StencilDev& S, float* ws) {
     float* partial = (float*)((char*)ws + walk_ws_bytes(a, S));
@@ -801,6 +978,7 @@ DISCO_BOUNDS_READER(bounds_flag_stencil)
 
 hipError_t launch_stencil_blocked(const ExecArgs& a, const StencilDev& S, float* ws) {
     if (S.tile != kStencilSmallTile && S.tile != kStencilTile) return hipErrorInvalidValue;
+    if (a.dw) return a.dtype == 1 ? fold_grad<uint16_t>(a, S, ws) : fold_grad<float>(a, S, ws);
     return a.dtype == 1 ? stencil_blocked_parts<uint16_t>(a, S, ws) : stencil_blocked_parts<float>(a, S, ws);
 }
 

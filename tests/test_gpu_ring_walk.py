@@ -96,3 +96,46 @@ def test_spectral_rings_of_two_lengths(case, op, chans, monkeypatch):
     assert err <= 1e-5
     assert np.abs(y - ref).max() <= 1e-5 * np.abs(ref).max()
     plan.close()
+
+
+@pytest.mark.parametrize("basis", list(K))
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("case", [(64, 128, 64, 128, "cell_centred", False), (65, 128, 65, 128, "poles", False),
+                                  (64, 128, 32, 64, "cell_centred", True), (64, 512, 64, 512, "cell_centred", False)],
+                         ids=lambda c: "%dx%d_%dx%d_%s_%s" % c)
+def test_depthwise_weight_gradient_by_correlation(case, dtype, basis):
+    """dW from the correlations of dy and x (ring walk and frequency domain),
+    an odd number of channels and a batch, against the oracle: sums of up to
+    2 x 64 x 512 fp32 products with random signs, 1e-5 as the other gradient
+    tests; bf16 inputs are exact and the sums fp32, so only dW's own rounding
+    (2^-9 relative) adds."""
+    import oracle
+    import torch
+    a, b, c, d, smp, transpose = case
+    tc = 3 * math.pi / (min(a, c) - (smp == "poles"))
+    if b == 8 * a:
+        tc = 1.5 * math.pi / a  # narrower windows on the stretched grid
+    C = 5
+    r = np.random.default_rng(73)
+    xs, ys = ((2, C, c, d), (2, C, a, b)) if transpose else ((2, C, a, b), (2, C, c, d))
+    x = synth.to_storage(r.standard_normal(xs), dtype)
+    dy = synth.to_storage(r.standard_normal(ys), dtype)
+    w = synth.to_storage(r.standard_normal((C, K[basis])), dtype)
+    say("correlated dW", case, basis, dtype)
+    plan = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp, backward=True)
+    fn = disco.transpose_depthwise_backward if transpose else disco.forward_depthwise_backward
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    _, dw = fn(plan, torch_dev(x, dtype), torch_dev(w, dtype), torch_dev(dy, dtype), want_dx=False)
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    assert "walk_grad" in ran and "spectral_grad" in ran
+    full = oracle.default().weight_grad(a, b, c, d, tc, x.astype(np.float64), dy.astype(np.float64),
+                                        transpose=transpose, basis=list(K).index(basis),
+                                        sampling=1 if smp == "poles" else 0)
+    ref = np.stack([full[ch, ch] for ch in range(C)])
+    err = rel_l2(to_numpy(dw), ref)
+    say("  rel_l2 %.3e" % err)
+    assert err <= (1e-5 if dtype == "fp32" else 4e-3)
+    plan.close()
