@@ -368,6 +368,7 @@ disco_status_t upload_mfma(const MfmaHost& H, MfmaDev* d) {
     if ((s = upload_vec(H.red_pattern, &P.red_pattern, &d->bytes, "hipMalloc(reduce)")) != DISCO_OK) return s;
     if ((s = upload_vec(H.red_ptr, &P.red_ptr, &d->bytes, "hipMalloc(reduce)")) != DISCO_OK) return s;
     if ((s = upload_vec(H.red_slots, &P.red_slots, &d->bytes, "hipMalloc(reduce)")) != DISCO_OK) return s;
+    d->pair = H.pair;
     d->n_segs = (int32_t)H.segs.size();
     d->n_order = (int32_t)H.order.size();
     d->n_qtiles = H.n_qtiles;

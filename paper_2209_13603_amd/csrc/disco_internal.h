@@ -419,15 +419,31 @@ struct SpectralDev {
 // k_reduce_partials.
 constexpr int kMfmaTile = 256;       // output longitudes per workgroup
 constexpr int kMfmaCis = 8;          // input channels staged per pass
-constexpr int kMfmaMaxChunks = 8;    // chunks (32 offsets each) of one segment
-constexpr int kMfmaMaxElems = 1280;  // staged elements per channel of one segment
+constexpr int kMfmaChunks = 8;       // chunks (32 offsets each) of one segment
+constexpr int kMfmaElems = 1280;     // staged elements per channel of one segment
+// Natural pairs (MfmaHost::pair, k_mfma_pair): at even strides groups start at
+// even offsets, so that the eight inputs of a lane are four aligned pairs, and
+// the inputs are staged as they lie (2 bytes each instead of 4).  With two
+// channels per pass a segment then holds all the rings an output ring reads;
+// the duplicated elements of eight channels cut an equatorial ring of the
+// 512 x 1024 -> 256 x 512 op into seven segments, each writing fp32 partial
+// outputs.  Grids of fewer than 128 (ring, tile) workgroups per batch item
+// keep the other layout, whose segments and longer passes fill the chip
+// (64 x 128 -> 32 x 64, 20 -> 30 channels: 43 us against 52 us).
+constexpr int kMfmaPairCis = 2, kMfmaPairChunks = 16, kMfmaPairElems = 8192;
+constexpr int kMfmaMaxChunks = kMfmaPairChunks, kMfmaMaxElems = kMfmaPairElems;  // of either layout
+inline bool mfma_pair(const OpGeom& g) {
+    return g.stride % 2 == 0 && (int64_t)g.nlat_o * ((g.nq + kMfmaTile - 1) / kMfmaTile) >= 128;
+}
 // Spans use PSpan: row = ring * nlon_i, dstart (a multiple of 8), len and
-// lds_base in staged elements (element e of a span holds the two inputs at
-// longitudes s q0 + dstart + e and + 1, q0 the tile's first output longitude).
+// lds_base in elements (element e of a span is the input at longitude s q0 +
+// dstart + e, q0 the tile's first output longitude; unless `pair`, it is
+// staged with the one after it).
 struct MSeg { int32_t ring, chunk_begin, chunk_end, span_begin, span_end, n_elems, slot, pad; };
 struct MChunkHdr { int32_t grp[4]; };  // staged element of each group's offset d0 at q = q0
 struct MfmaHost {
     int32_t P = 1;
+    bool pair = false;   // natural-pair layout
     std::vector<PSpan> spans;
     std::vector<MSeg> segs;
     std::vector<MChunkHdr> chunks;
@@ -464,6 +480,7 @@ struct PackedDev {
 };
 
 struct MfmaDev {
+    bool pair = false;
     PSpan* spans = nullptr;
     MSeg* segs = nullptr;
     MChunkHdr* chunks = nullptr;

@@ -751,6 +751,8 @@ int pack_mfma(const HostOp& op, MfmaHost* out, std::string* err) {
     const int halo = s * (kMfmaTile - 1);
     MfmaHost H;
     H.P = P;
+    H.pair = mfma_pair(g);
+    const int max_chunks = H.pair ? kMfmaPairChunks : kMfmaChunks, max_elems = H.pair ? kMfmaPairElems : kMfmaElems;
     for (int to = 0; to < g.nlat_o; ++to) {
         // 1. Offsets (mod nlon_i) of every input ring, over all phases.
         std::vector<std::vector<int32_t>> ring_d((size_t)g.nlat_i);
@@ -774,7 +776,11 @@ int pack_mfma(const HostOp& op, MfmaHost* out, std::string* err) {
                     gap = ds[i] - ds[i - 1];
                     a0 = ds[i];
                 }
-            const int32_t width = N - gap + 1;
+            int32_t width = N - gap + 1;
+            if (H.pair && a0 % 2 != 0) {  // groups start at even offsets
+                --a0;
+                width = std::min(width + 1, N);
+            }
             const int ng = (width + 7) / 8;
             arc_start[(size_t)ti] = a0;
             first_group[(size_t)ti] = (int32_t)groups.size();
@@ -815,8 +821,8 @@ int pack_mfma(const HostOp& op, MfmaHost* out, std::string* err) {
             return total;
         };
         for (size_t i = 0; i < groups.size(); ++i) {
-            if (!segs.empty() && (int)(i - segs.back().g0) < 4 * kMfmaMaxChunks &&
-                seg_elems(segs.back().g0, i + 1) <= kMfmaMaxElems) {
+            if (!segs.empty() && (int)(i - segs.back().g0) < 4 * max_chunks &&
+                seg_elems(segs.back().g0, i + 1) <= max_elems) {
                 segs.back().g1 = i + 1;
             } else {
                 segs.push_back(Seg{i, i + 1});
