@@ -180,6 +180,27 @@ int spectral_min_entries() {
     return 128;
 }
 
+// The environment variable above also lifts the lines on sizes below which
+// the spectral, walk and correlation paths are left to the direct kernels.
+bool lines_lifted() {
+    const char* v = std::getenv("DISCO_SPECTRAL_MIN_ENTRIES");
+    return v && *v;
+}
+
+// 3x3 ops between grids of different longitudes take the spectral path from
+// 2^19 pixels of the larger grid on: its products are a chain over input rings
+// and channels on few rings, whose time hardly falls with the grid, beside
+// direct sums that do (16 channels, 2 items: 128 x 256 from 64 x 128 45 us
+// without and 100 us with, 256 x 512 from 128 x 256 83 and 119 us, 512 x 1024
+// from 256 x 512 302 and 278 us; 32 -> 32 channels 192 and 234, 792 and 701 us).
+// The other bases use the tables on one-channel items only (fold_spectral).
+constexpr int64_t kTwoLengthPixels = 1 << 19;
+bool spectral_pays(const HostOp& h) {
+    const OpGeom& g = h.g;
+    if (h.basis != DISCO_BASIS_BILINEAR_3X3 || (g.P == 1 && g.stride == 1) || lines_lifted()) return true;
+    return std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o) >= kTwoLengthPixels;
+}
+
 disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
     disco_status_t s;
     if ((s = upload_vec(S.rings, &d->rings, &d->bytes, "hipMalloc(spectral rings)")) != DISCO_OK) return s;
@@ -456,7 +477,9 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
     // stride is 1.  The spectral and sweep layouts are built for the 3x3 basis.
     std::vector<uint8_t> heavy;
     std::string err;
-    int rc = build_spectral(h, spectral_min_entries(), &T->sp, &heavy, &err, true);
+    int rc = DISCO_OK;
+    if (spectral_pays(h)) rc = build_spectral(h, spectral_min_entries(), &T->sp, &heavy, &err, true);
+    else heavy.assign((size_t)h.g.n_patterns(), 0);
     if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
     d->n_heavy_rings = (int32_t)T->sp.rings.size();
     int64_t core = 0;
@@ -666,7 +689,6 @@ struct Dispatch {
 // The small-op rule of AUTO: below 2^18 output pixel-channels one launch of
 // the general kernel over every ring (launch latency dominates), else the
 // fused schedule.
-constexpr int64_t kFoldSpectralPixels = 1 << 21;
 int32_t resolve_auto(const DeviceOp& op, int32_t algo, int64_t Co) {
     if (algo != DISCO_ALGO_AUTO) return algo;
     const double out_pix_chan = (double)Co * op.g.nlat_o * op.g.nlon_o;
@@ -676,14 +698,23 @@ int32_t resolve_auto(const DeviceOp& op, int32_t algo, int64_t Co) {
 // Whether a folded-weight call of one-channel items (Ci = Co = 1, `items` of
 // them) walks the rings with narrow windows (stride-1 ops whose layout has
 // a walk), and whether the others then take the spectral path beside it
-// instead of the blocked kernel: from 2^21 output pixels on (below, the three
-// launches and the fork cost more than the polar rings' direct sums: 513 x
-// 1024, one item, 38 us without and 75 us with).  DISCO_ALGO_FUSED_DIRECT keeps the
-// direct sums everywhere.
-bool fold_walk(const DeviceOp& op, int64_t Ci, int64_t Co) { return op.has_walk && Ci == 1 && Co == 1; }
+// instead of the blocked kernel.  The walk has one launch more (the weights),
+// and pays from 2^22 output pixels on, or from 2^20 where they are at least 64
+// items (128 x 256, 32 items: 37 us without, 47 us with; 256 x 512, 4 items, 38
+// and 48 us; 64 x 128, 128 items, 55 and 49 us; 256 x 512, 128 items, 178 and 113
+// us).  The spectral path's three launches and fork pay from 2^23 on (256 x
+// 512, 32 items: 59 us without either, 79 us with both; 512 x 1024, 4 items, 42
+// and 74 us, 32 items 188 and 108 us).  DISCO_ALGO_FUSED_DIRECT keeps the
+// direct sums of the wide rings everywhere.
+constexpr int64_t kFoldWalkPixels = 1 << 22, kFoldWalkPixelsManyItems = 1 << 20, kFoldSpectralPixels = 1 << 23;
+bool fold_walk(const DeviceOp& op, int64_t items, int64_t Ci, int64_t Co) {
+    const int64_t pixels = items * op.g.nlat_o * op.g.nlon_o;
+    return op.has_walk && Ci == 1 && Co == 1 &&
+           (pixels >= (items >= 64 ? kFoldWalkPixelsManyItems : kFoldWalkPixels) || lines_lifted());
+}
 bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
-    return fold_walk(op, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
-           items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels;
+    return fold_walk(op, items, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
+           (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || lines_lifted());
 }
 // Items assumed where a call is not at hand (plan creation, work figures):
 // a depthwise call's.
@@ -960,7 +991,7 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     const PackedDev* packed_set = axisym ? &op.packed : dp.packed;
     // One output channel on a stride-1 op takes the blocked stencil kernel.
     const bool blocked = axisym && op.stencil.P.n_items > 0 && Co == 1;
-    a.walk = blocked && fold_walk(op, Ci, Co);
+    a.walk = blocked && fold_walk(op, B, Ci, Co);
     size_t ws_spec = 0, ws_sweep = 0, ws = 0;
     auto workspace = [&] {
         ws_spec = heavy_spectral || spectral ? (workspace_bytes_spectral(a) + 255) / 256 * 256 : 0;
@@ -1211,8 +1242,12 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
     // One-channel items (depthwise calls, a single channel of the other
     // bases): correlations of dy and x instead of gathered sums, where the
     // op's rings are covered by the walk and the spectral tables.
+    // The nine sums of the 3x3 basis come from one fp32 sweep and stay the
+    // better path below 2^22 pixels (512 x 1024, 4 items: 165 us against 182).
+    const bool few = op.basis == DISCO_BASIS_BILINEAR_3X3 && x->dtype == DISCO_FLOAT32 && !lines_lifted() &&
+                     B * C_x * op.g.nlat_o * op.g.nlon_o < kFoldWalkPixels;
     const bool folded = (depthwise || (op.basis != DISCO_BASIS_BILINEAR_3X3 && C_x == 1 && C_dy == 1)) && op.has_walk &&
-                        (op.n_entries_wide == 0 || op.n_heavy_rings > 0);
+                        (op.n_entries_wide == 0 || op.n_heavy_rings > 0) && !few;
     if (folded) {
         const int parts = kPartStencil | (op.n_heavy_rings > 0 ? kPartCore : 0);
         if ((s = ensure_parts(plan, op, parts)) != DISCO_OK) return s;
@@ -1456,7 +1491,7 @@ disco_status_t disco_plan_create(int nlat_in, int nlon_in, int nlat_out, int nlo
         const OpTables* T = d.tables.get();
         const bool bare = T && (d.g.P > 1 || d.g.stride > 1 || (T->sp.rings.empty() && !T->has_sweep));
         return d.basis != DISCO_BASIS_BILINEAR_3X3 ? (needed_parts(d, DISCO_ALGO_AUTO, true) |
-                                                      (fold_spectral(d, DISCO_ALGO_AUTO, kTypicalItems, 1, 1) ? kPartCore : 0))
+                                                      (d.has_walk && d.n_heavy_rings > 0 ? kPartCore : 0))
                                                    : (kPartCore | (small || bare ? kPartDirect : 0));
     };
     for (DeviceOp* d : {&plan->fwd, &plan->tr, &plan->fwd_adj, &plan->tr_adj})
@@ -1638,7 +1673,7 @@ disco_status_t disco_kernel_work(disco_plan_t plan, int32_t transpose, int32_t a
             // Folded psi: one value per (output pixel, input pixel) pair.
             const int64_t light = op.n_entries - op.n_entries_wide, nq = op.g.nq;
             const bool blocked = op.stencil.P.n_items > 0 && c_out == 1;
-            const bool walk = blocked && fold_walk(op, c_in, c_out);
+            const bool walk = blocked && fold_walk(op, kTypicalItems, c_in, c_out);
             const bool heavy = walk && fold_spectral(op, dp.algo, kTypicalItems, c_in, c_out);
             if (heavy) {
                 spectral_rows(op.spectral, &rows);

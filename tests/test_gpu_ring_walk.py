@@ -2,8 +2,9 @@
 (one-channel items, stride-1 ops), and the spectral path of ops whose two
 grids have different ring lengths.
 
-A depthwise call of enough items takes the walk and the spectral path; the
-same channel alone is far below that line and, with algo fused_direct, sums
+A depthwise call past the lines on sizes (lifted here) takes the walk and the
+spectral path; the
+same channel alone, with algo fused_direct, sums
 every ring directly (checked against the fp64 oracle on small grids by the
 other tests).  The two differ by the rounding of sums of up to 128 products
 and of two transforms of at most 512 points in fp32: 2^-24 sqrt(128) and
@@ -21,7 +22,7 @@ from paper_2209_13603_amd import disco, synth
 pytestmark = pytest.mark.gpu
 
 K = {"bilinear3x3": 9, "axisym4": 4, "separable4x4": 16}
-# (nlat_in, nlon_in, nlat_out, nlon_out, sampling, op, batch, channels): at least 2^21 outputs
+# (nlat_in, nlon_in, nlat_out, nlon_out, sampling, op, batch, channels)
 CASES = [
     (128, 256, 128, 256, "cell_centred", "forward", 1, 64),    # one tile, wrapped both ways
     (128, 256, 128, 256, "cell_centred", "forward", 3, 23),    # odd channel and batch groups
@@ -36,8 +37,9 @@ CASES = [
 @pytest.mark.parametrize("basis", list(K))
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%dx%d_%dx%d_%s_%s_%dx%d" % c)
-def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis):
+def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis, monkeypatch):
     import torch
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "128")  # the default; lifts the lines on sizes
     a, b, c, d, smp, op, B, C = case
     tc = 3 * math.pi / (min(a, c) - (smp == "poles"))
     xs = (B, C, a, b) if op == "forward" else (B, C, c, d)
@@ -103,7 +105,7 @@ def test_spectral_rings_of_two_lengths(case, op, chans, monkeypatch):
 @pytest.mark.parametrize("case", [(64, 128, 64, 128, "cell_centred", False), (65, 128, 65, 128, "poles", False),
                                   (64, 128, 32, 64, "cell_centred", True), (64, 512, 64, 512, "cell_centred", False)],
                          ids=lambda c: "%dx%d_%dx%d_%s_%s" % c)
-def test_depthwise_weight_gradient_by_correlation(case, dtype, basis):
+def test_depthwise_weight_gradient_by_correlation(case, dtype, basis, monkeypatch):
     """dW from the correlations of dy and x (ring walk and frequency domain),
     an odd number of channels and a batch, against the oracle: sums of up to
     2 x 64 x 512 fp32 products with random signs, 1e-5 as the other gradient
@@ -111,6 +113,7 @@ def test_depthwise_weight_gradient_by_correlation(case, dtype, basis):
     (2^-9 relative) adds."""
     import oracle
     import torch
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "128")  # the default; lifts the lines on sizes
     a, b, c, d, smp, transpose = case
     tc = 3 * math.pi / (min(a, c) - (smp == "poles"))
     if b == 8 * a:
