@@ -575,7 +575,7 @@ def _events(torch, disco, fn, steps):
 
 def bench_backward(args, wl, plan, x, w, es, torch, disco):
     """Gradient step of the workload's op (App. C): dx through the adjoint op
-    and dW from the gathered sums.  value = output pix x chan of the op per
+    and dW from the gathered sums or, for one-channel items, correlations.  value = output pix x chan of the op per
     second of one gradient step (dx and dW).  Kernel figures from two passes
     with kernel events, dx alone and dW alone (their kernels share names)."""
     from types import SimpleNamespace
@@ -609,7 +609,21 @@ def bench_backward(args, wl, plan, x, w, es, torch, disco):
                 rings = spec["rings"]
                 b_ = B * Co * rings * (n_o * 4 + (n_o // 2 + 1) * 8)
                 f_, bd = B * Co * rings * fft_flops(n_o), "alu"
+            elif k == "walk_grad":
+                # one-channel items: one product per stored (output pixel,
+                # input pixel) pair, x and dy read
+                o_, i_, pairs = work["stencil_walk" if "stencil_walk" in work else "stencil_blocked"]
+                b_, f_, bd = B * Ci * (i_ + o_) * es, 2.0 * pairs * B * Ci, "alu"
+            elif k == "spectral_grad":
+                n_o, n_i = (wl.nlon_out, wl.nlon_in) if wl.op == "forward" else (wl.nlon_in, wl.nlon_out)
+                mf = max(n_o, n_i) // 2 + 1
+                b_ = 8 * B * Ci * (spec["pairs"] * (n_i // 2 + 1) + spec["rings"] * (n_o // 2 + 1)) + K * 4 * spec["pairs"] * mf
+                f_, bd = (8.0 + 2.0 * K) * B * Ci * spec["pairs"] * mf, "alu"
+            elif k == "walk_grad_contract":
+                b_, f_, bd = 0, 0.0, "hbm"
             else:
+                if k == "spectral_rfft" and k not in work:
+                    work = dict(work, spectral_rfft=(0, 0, 0))  # its figures come from spec
                 if k not in work:
                     raise SystemExit("no work figures for kernel %s" % k)
                 mm = kernel_model(k, model_wl, work[k], es, spec)
@@ -620,20 +634,25 @@ def bench_backward(args, wl, plan, x, w, es, torch, disco):
             if bd == "hbm":
                 row["hbm_frac"] = round(b_ / (avg / 1e3) / 1e9 / HBM_PEAK_GBS, 4)
             kernels["%s:%s" % (tag, k)] = row
-            if not k.startswith("spectral_") and k != "weight_grad_reduce":
+            if not k.startswith("spectral_") and k not in ("weight_grad_reduce", "walk_grad_contract"):
                 cands.append(("%s:%s" % (tag, k), tot_ms, b_, f_, bd, avg))
 
     # dx: the adjoint op has the other op's filter pairs (its work figures).
     work_dx = plan.kernel_work(not transpose, "auto", Co, Ci, wl.dtype)
-    grids = dict(nlon_in=wl.nlon_in, nlon_out=wl.nlon_out)
+    grids = dict(nlon_in=wl.nlon_in, nlon_out=wl.nlon_out, basis=wl.basis, K=K)
     # (the adjoint op's spectral rings are those of the other op's filter pairs)
     add("dx", kt_dx, work_dx, SimpleNamespace(batch=B, c_in=Co, c_out=Ci, op="forward" if transpose else "transpose",
                                               **grids), spectral_spec(plan, not transpose))
-    # dW: one-pass gathered sums (fp32, 3x3 basis) or the op's kernels per channel.
+    # dW: one-pass gathered sums (fp32, 3x3 basis), correlations (one channel
+    # of the other bases) or the op's kernels per channel.
     if wl.dtype == "fp32" and wl.basis == "bilinear3x3":
         work_dw = plan.kernel_work(transpose, "gather_then_contract", Ci, Ci * K, wl.dtype)
         mwl = SimpleNamespace(batch=B, c_in=Ci, c_out=Ci * K, op=wl.op, **grids)
         spec_dw = dict(spectral_spec(plan, transpose), z_mode=True)
+    elif "walk_grad" in kt_dw:
+        work_dw = plan.kernel_work(transpose, "auto", 1, 1, wl.dtype)
+        mwl = SimpleNamespace(batch=B, c_in=1, c_out=1, op=wl.op, **grids)
+        spec_dw = spectral_spec(plan, transpose)
     else:
         work_dw = plan.kernel_work(transpose, "auto", 1, K, wl.dtype)
         mwl = SimpleNamespace(batch=B * Ci, c_in=1, c_out=K, op=wl.op, **grids)

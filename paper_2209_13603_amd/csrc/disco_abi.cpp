@@ -716,9 +716,9 @@ bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, 
     return fold_walk(op, items, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
            (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || lines_lifted());
 }
-// Items assumed where a call is not at hand (plan creation, work figures):
-// a depthwise call's.
-constexpr int64_t kTypicalItems = 8;
+// Items assumed where a call is not at hand (work figures): one of the
+// axisymmetric basis (App. B's layer), a depthwise call's of the others.
+int64_t typical_items(const DeviceOp& op) { return op.basis == DISCO_BASIS_AXISYMMETRIC_4 ? 1 : 32; }
 
 Dispatch dispatch(const DeviceOp& op, int32_t algo, int Ci, int Co, int32_t dtype) {
     const OpGeom& g = op.g;
@@ -1673,8 +1673,8 @@ disco_status_t disco_kernel_work(disco_plan_t plan, int32_t transpose, int32_t a
             // Folded psi: one value per (output pixel, input pixel) pair.
             const int64_t light = op.n_entries - op.n_entries_wide, nq = op.g.nq;
             const bool blocked = op.stencil.P.n_items > 0 && c_out == 1;
-            const bool walk = blocked && fold_walk(op, kTypicalItems, c_in, c_out);
-            const bool heavy = walk && fold_spectral(op, dp.algo, kTypicalItems, c_in, c_out);
+            const bool walk = blocked && fold_walk(op, typical_items(op), c_in, c_out);
+            const bool heavy = walk && fold_spectral(op, dp.algo, typical_items(op), c_in, c_out);
             if (heavy) {
                 spectral_rows(op.spectral, &rows);
                 rows[1].w.pairs = op.n_entries_wide * nq;

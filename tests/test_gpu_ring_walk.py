@@ -3,9 +3,8 @@
 grids have different ring lengths.
 
 A depthwise call past the lines on sizes (lifted here) takes the walk and the
-spectral path; the
-same channel alone, with algo fused_direct, sums
-every ring directly (checked against the fp64 oracle on small grids by the
+spectral path; the same channel alone, below the lines and with algo
+fused_direct, sums every ring directly (checked against the fp64 oracle on small grids by the
 other tests).  The two differ by the rounding of sums of up to 128 products
 and of two transforms of at most 512 points in fp32: 2^-24 sqrt(128) and
 2^-24 log2(512) relative to the ring's values, 1e-6 together; bf16 outputs by
@@ -54,6 +53,7 @@ def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis, monkeypatc
     ran = disco.kernel_timing_read()
     disco.kernel_timing(False)
     assert "stencil_walk" in ran and "spectral_mac" in ran
+    monkeypatch.delenv("DISCO_SPECTRAL_MIN_ENTRIES")  # back below the lines
     for ch in (0, C // 2, C - 1):
         for bi in (0, B - 1):
             xc = xt[bi:bi + 1, ch:ch + 1].contiguous()
