@@ -622,8 +622,8 @@ def bench_backward(args, wl, plan, x, w, es, torch, disco):
             elif k == "walk_grad_contract":
                 b_, f_, bd = 0, 0.0, "hbm"
             else:
-                if k == "spectral_rfft" and k not in work:
-                    work = dict(work, spectral_rfft=(0, 0, 0))  # its figures come from spec
+                if k in ("spectral_rfft", "reduce_partials") and k not in work:
+                    work = dict(work, **{k: (0, 0, 0)})  # figures from spec; sums of partial outputs
                 if k not in work:
                     raise SystemExit("no work figures for kernel %s" % k)
                 mm = kernel_model(k, model_wl, work[k], es, spec)
