@@ -263,7 +263,9 @@ struct WalkHost {
     int32_t back = 0, ahead = 0;      // a tile at q0 stages columns of [q0 - back, q0 + ahead)
 };
 // Covers every pattern not in `wide`, if these are consecutive rings whose
-// windows fit the slots; otherwise leaves *out without steps.
+// windows fit the slots and hold an entry at all (then pieces, quads and
+// groups are not empty, though single steps may have none); otherwise leaves
+// *out without steps.
 int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out, std::string* err);
 
 struct WalkDev {

@@ -712,6 +712,10 @@ int pack_walk(const HostOp& op, const std::vector<uint8_t>& wide, WalkHost* out,
         }
         H.steps.push_back(S);
     }
+    // Cutoffs below the ring spacing can leave every pattern without entries:
+    // the blocked kernel writes the zeros.  (A step without entries among
+    // others has no pieces and writes its zeros here.)
+    if (H.pieces.empty()) return DISCO_OK;
     *out = std::move(H);
     return DISCO_OK;
 }

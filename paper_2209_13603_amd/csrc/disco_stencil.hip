@@ -671,11 +671,12 @@ __device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* 
     // Step descriptors run two steps ahead of their use, a step's pieces
     // (lane i holds piece i), weights and new rings one step.
     WStep N = steps[s0 + 1 < s1 ? s0 + 1 : s0];
-    int desc = pieces[S.piece + (lane < S.n ? lane : 0)];
+    // A step without entries has none, and may begin past the last one.
+    int desc = lane < S.n ? pieces[S.piece + lane] : 0;
     for (int s = s0; s < s1; ++s) {
         const WStep N2 = steps[s + 2 < s1 ? s + 2 : s1 - 1];
         const int fresh = N.hi - S.hi;  // rings new to the next step's window
-        const int desc_next = pieces[N.piece + (lane < N.n ? lane : 0)];
+        const int desc_next = lane < N.n ? pieces[N.piece + lane] : 0;
         float4 wv[kWalkW4], pf[kWalkAhead][kWalkLoads];
         load_weights(N, wv);
 #pragma unroll

@@ -185,6 +185,100 @@ void check_sweep(const HostOp& op, const SweepHost& sw, const std::string& what)
     if (got != want) fail("values differ from the op's");
 }
 
+// The ring walk, staged as its kernel stages it (runs of `run_len` steps, ring
+// t in slot t mod n_slots from column q0 + ring_start on): every entry of the
+// covered patterns is met exactly once, at its own input pixel and with its own
+// values, everything else is zero, reads stay inside the slots, and the
+// quads of the gradient's groups name each run of four weights once.
+void check_walk(const HostOp& op, int min_entries, const std::string& what) {
+    const OpGeom& g = op.g;
+    const std::vector<uint8_t> wide = wide_patterns(op, min_entries);
+    WalkHost H;
+    std::string err;
+    check(pack_walk(op, wide, &H, &err), what + " pack_walk", err);
+    if (H.steps.empty()) return;
+    auto fail = [&](const char* m) {
+        std::printf("FAIL %s: ring walk: %s\n", what.c_str(), m);
+        ++failures;
+    };
+    const int N = g.nlon_i, p0 = H.steps[0].pat, lags_pats = kWalkLags * kWalkPats;
+    if (H.pieces.empty() || H.quads.empty() || H.groups.empty()) return fail("steps but no pieces");
+    if (H.vals.size() != H.pieces.size() * lags_pats || H.cells.size() != H.vals.size()) return fail("weights per piece");
+    if (H.pitch % 4 != 0 || H.pitch > kWalkMaxPitch || H.n_slots * H.pitch > kWalkMaxFloats) return fail("slots over their budget");
+    for (int p = 0; p < g.n_patterns(); ++p)
+        if ((p >= p0 && p < H.pat_end) == (bool)wide[(size_t)p]) return fail("covered patterns are not the narrow ones");
+    std::map<std::tuple<int, int, int>, int64_t> entry;  // (pattern, input ring, offset mod N)
+    for (int p = p0; p < H.pat_end; ++p)
+        for (int32_t e = op.pat_ptr[(size_t)p]; e < op.pat_ptr[(size_t)p + 1]; ++e)
+            entry[{p, op.t_in[(size_t)e], op.d[(size_t)e]}] = e;
+    size_t stored = 0;
+    for (const PVal& v : H.vals) stored += v.v[0] != 0 || v.v[1] != 0 || v.v[2] != 0 || v.v[3] != 0;
+    if (stored != entry.size()) return fail("weights and entries differ in number");
+    const int ns = (int)H.steps.size(), n_tiles = (g.nq + kWalkTile - 1) / kWalkTile;
+    for (int run_len : {1, 3, ns})
+        for (int tile = 0; tile < n_tiles; tile += std::max(1, n_tiles - 1)) {
+            const int q0 = tile * kWalkTile;
+            size_t met = 0;
+            for (int s0 = 0; s0 < ns; s0 += run_len) {
+                std::vector<int64_t> lds((size_t)H.n_slots * H.pitch, -1);  // input pixel of each column
+                int staged = H.steps[(size_t)s0].lo;
+                for (int s = s0; s < std::min(ns, s0 + run_len); ++s) {
+                    const WStep& S = H.steps[(size_t)s];
+                    if (S.lo < 0 || S.hi > g.nlat_i || S.lo > S.hi || S.hi - S.lo > H.n_slots || S.pat != p0 + kWalkPats * s)
+                        return fail("a step's window");
+                    if (S.n < 0 || S.n > kWalkPieces || S.piece + S.n > (int)H.pieces.size()) return fail("a step's pieces");
+                    for (; staged < S.hi; ++staged)
+                        for (int c = 0; c < H.pitch; ++c)
+                            lds[(size_t)(staged % H.n_slots) * H.pitch + c] =
+                                (int64_t)staged * N + (q0 + H.ring_start[(size_t)staged] + c) % N;
+                    for (int i = 0; i < S.n; ++i) {
+                        const int col = H.pieces[(size_t)(S.piece + i)] >> 5, lags = H.pieces[(size_t)(S.piece + i)] & 31;
+                        if (col % 4 != 0 || lags < 1 || lags > kWalkLags) return fail("a piece's column or length");
+                        if (col % H.pitch + kWalkTile - 1 + lags - 1 >= H.pitch) return fail("a piece reads past its slot");
+                        for (int j = 0; j < kWalkLags; ++j)
+                            for (int r = 0; r < kWalkPats; ++r) {
+                                const size_t at = ((size_t)(S.piece + i) * kWalkLags + j) * kWalkPats + r;
+                                const PVal& v = H.vals[at];
+                                const bool zero = v.v[0] == 0 && v.v[1] == 0 && v.v[2] == 0 && v.v[3] == 0;
+                                if (j >= lags || S.pat + r >= H.pat_end) {
+                                    if (!zero) return fail("a value past the piece or the last pattern");
+                                    continue;
+                                }
+                                const int64_t at0 = lds[(size_t)col + j];
+                                if (at0 < 0) return fail("a column of a ring that is not staged");
+                                const auto it = entry.find({S.pat + r, (int)(at0 / N), (int)(((at0 % N - q0) % N + N) % N)});
+                                // (A window of the whole ring meets an input pixel at two lags: one is zero.)
+                                if (zero) continue;
+                                if (it == entry.end()) return fail("a value without an entry");
+                                ++met;
+                                for (int q : {1, 6, 131, kWalkTile - 1})
+                                    if (lds[(size_t)col + j + q] != at0 / N * N + (at0 % N + q) % N) return fail("columns out of order");
+                                int cell = 0;
+                                float w[4];
+                                if (!entry_cell_values(op, it->second, &cell, w)) return fail("an entry outside its cell");
+                                if (std::memcmp(w, v.v, sizeof(w)) != 0 || cell != H.cells[at]) return fail("an entry's values");
+                            }
+                    }
+                }
+            }
+            if (met != entry.size()) return fail("entries missing or met twice");
+        }
+    size_t q = 0;
+    for (const WGroup& G : H.groups) {
+        if (G.n < 1 || G.n > kWalkQuads || G.quad != (int)q || G.step < 0 || G.step >= ns) return fail("a group's quads");
+        const WStep& S = H.steps[(size_t)G.step];
+        for (int k = 0; k < G.n; ++k, ++q) {
+            const int piece = H.quads[q].w / lags_pats, lag = H.quads[q].w % lags_pats / kWalkPats;
+            if (piece < S.piece || piece >= S.piece + S.n || lag % 4 != 0 ||
+                H.quads[q].col != (H.pieces[(size_t)piece] >> 5) + lag)
+                return fail("a quad's column or weight");
+        }
+    }
+    size_t want = 0;
+    for (int32_t p : H.pieces) want += (size_t)((p & 31) + 3) / 4;
+    if (q != want || q != H.quads.size()) return fail("quads missing");
+}
+
 void check_mfma(const HostOp& op, const std::string& what) {
     MfmaHost M;
     std::string err;
@@ -321,6 +415,8 @@ void run_op(const PlanParams& p, bool transpose, bool quad_at_output, const char
             StencilHost S;
             check(pack_stencil(op, 256, tile, &S, &err), what + " pack_stencil", err);
         }
+        check_walk(op, 128, what);
+        check_walk(op, 32, what + " (32 entries)");
     }
     if (op.basis != DISCO_BASIS_BILINEAR_3X3) return;
     check_mfma(op, what);
@@ -441,6 +537,12 @@ int main(int argc, char** argv) {
         const double tc = 3 * pi / (std::min(c[0], c[2]) - 1);
         for (int basis : {0, 1, 2}) run_plan(c[0], c[1], c[2], c[3], tc, basis, 0, 1, 0.0);
     }
+    // Cutoffs below the ring spacing: ops without an entry, and ops with some
+    // output rings (the last ones among them) without entries.
+    const int sparse[][4] = {{64, 128, 32, 64}, {64, 128, 33, 64}, {32, 64, 64, 64}, {33, 64, 64, 64}};
+    for (auto& c : sparse)
+        for (int basis : {0, 1, 2})
+            for (double tc : {0.1 * pi / 32, 0.02}) run_plan(c[0], c[1], c[2], c[3], tc, basis, 0, 0, 0.0);
     if (big) run_plan(2048, 4096, 2048, 4096, 3 * pi / 2048, 0, 0, 0, 0.0);
     run_abi();
     std::printf("%s (%d failures)\n", failures ? "FAILED" : "OK", failures);

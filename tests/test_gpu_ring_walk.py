@@ -142,3 +142,41 @@ def test_depthwise_weight_gradient_by_correlation(case, dtype, basis, monkeypatc
     say("  rel_l2 %.3e" % err)
     assert err <= (1e-5 if dtype == "fp32" else 4e-3)
     plan.close()
+
+
+@pytest.mark.parametrize("basis", list(K))
+@pytest.mark.parametrize("case", [
+    (64, 128, 32, 64, 0.02, "transpose"),                          # no entry at all
+    (256, 256, 128, 256, 0.9 * math.pi / 512, "forward"),          # no entry at all, a latitude-only change
+    (64, 128, 33, 64, 0.1 * math.pi / 33, "transpose"),            # a few rings with entries, the last ones without
+], ids=lambda c: "%dx%d_%dx%d_%.3g_%s" % c)
+def test_cutoffs_below_the_ring_spacing(case, basis, monkeypatch):
+    """Output rings without entries are zero, and so is the gradient of filters
+    that meet no pixel, in depthwise calls past the lines on sizes."""
+    import oracle
+    import torch
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "128")  # the default; lifts the lines on sizes
+    a, b, c, d, tc, op = case
+    C = 3
+    r = np.random.default_rng(75)
+    xs, ys = ((2, C, a, b), (2, C, c, d)) if op == "forward" else ((2, C, c, d), (2, C, a, b))
+    x, dy, w = (r.standard_normal(sh).astype(np.float32) for sh in (xs, ys, (C, K[basis])))
+    say("sparse rings", case, basis)
+    plan = disco.Plan(a, b, c, d, tc, basis=basis, backward=True)
+    y = torch.full(ys, math.nan, device="cuda:0")
+    run = plan.forward_depthwise if op == "forward" else plan.transpose_depthwise
+    run(torch_dev(x), torch_dev(w), y=y)
+    full = oracle.depthwise_weights(w.astype(np.float64))
+    ref = run_oracle((a, b, c, d, tc), x, full, op, basis=list(K).index(basis))
+    assert np.abs(to_numpy(y) - ref).max() <= 1e-6 * max(1e-30, np.abs(ref).max())
+    fn = disco.forward_depthwise_backward if op == "forward" else disco.transpose_depthwise_backward
+    dx, dw = fn(plan, torch_dev(x), torch_dev(w), torch_dev(dy))
+    gw = oracle.default().weight_grad(a, b, c, d, tc, x.astype(np.float64), dy.astype(np.float64),
+                                      transpose=op == "transpose", basis=list(K).index(basis))
+    gw = np.stack([gw[ch, ch] for ch in range(C)])
+    say("  outputs zero: %s, dw zero: %s" % (not ref.any(), not gw.any()))
+    assert np.abs(to_numpy(dw) - gw).max() <= 1e-5 * max(1e-30, np.abs(gw).max())
+    assert np.isfinite(to_numpy(dx)).all()
+    if not ref.any():
+        assert not to_numpy(y).any() and not to_numpy(dw).any() and not to_numpy(dx).any()
+    plan.close()
