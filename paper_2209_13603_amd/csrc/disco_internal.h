@@ -679,6 +679,7 @@ inline size_t stencil_ws_bytes(const ExecArgs& a, const StencilDev& S) {
 // correlations of the narrow rings [split][channel][weight], the transforms
 // of x and dy on the wide ones, partial sums of dW [channel][chunk][K].
 constexpr int kFoldGradChunks = 32;    // partial sums per channel of the narrow rings' contraction
+constexpr int kFoldGradUnits = 32;     // (batch item, tile) sums that one wave adds up
 constexpr int kFoldGradSegments = 8;   // ... of each wide ring, over its bins
 struct FoldGradPlan {
     int splits = 1, chunks = 0;
@@ -690,9 +691,11 @@ inline FoldGradPlan fold_grad_plan(const ExecArgs& a, const StencilDev& S) {
     const int64_t C = a.dw_c > 0 ? a.dw_c : 1, K = basis_size(a.op->basis);
     const int64_t n_tiles = (a.op->g.nq + kWalkTile - 1) / kWalkTile, most = n_tiles * (a.B / C);
     // About 4096 waves: the (batch item, tile) sums of a group are split
-    // between waves when there are few groups and channels.
+    // between waves when there are few groups and channels, and so that no
+    // wave adds up more than kFoldGradUnits of them.
     int64_t splits = (4096 + S.walk.n_groups * C - 1) / (S.walk.n_groups * C);
-    splits = splits < 1 ? 1 : splits > most ? most : splits;
+    const int64_t least = (most + kFoldGradUnits - 1) / kFoldGradUnits;
+    splits = splits < least ? least : splits > most ? most : splits;
     p.splits = (int)(splits < 1 ? 1 : splits);
     const SpectralDev& D = a.op->spectral;
     const int64_t H = a.op->n_heavy_rings > 0 ? D.n_rings : 0;

@@ -800,7 +800,12 @@ hipError_t stencil_walk_launch(const ExecArgs& a, const StencilDev& S, float* fw
 // (group, channel, split): per tile it stages the step's rings and holds 16
 // dy operands (lane i + 4 b: pattern i, output 16 t + b), and one
 // v_mfma_f32_4x4x1_16b_f32 takes four patterns by four lags at 16 outputs; the
-// sixteen blocks' sums stay in registers until the end.  Per product one LDS
+// sixteen blocks' sums stay in registers until the end.  Rounding: a tile's
+// products of one block are two chains of eight, the tiles (at most
+// kFoldGradUnits, more are split between waves) are added to their sums; as
+// one chain over everything the gradient was further from its 64-bit value than
+// that of gathered sums (512 x 1024, 2 x 32 channels: 2.4e-7 against 2.0e-7;
+// now 1.4e-7, at the same speed).  Per product one LDS
 // read of 64 floats, which with the matrix cores bounds it.
 // grid: splits * C * n_groups workgroups of 64, dynamic LDS n_slots * pitch floats.
 template <typename T, int LOAD>
@@ -860,9 +865,13 @@ __global__ __launch_bounds__(64, 2) void k_walk_grad(const WGroup* __restrict__ 
             if (k >= G.n) continue;  // the same for every lane
             const int col = __builtin_amdgcn_readlane(mine.col, k) + xcol;
             DISCO_CHECK(col >= 0 && col + 240 < n_slots * pitch);
+            v4f even = {0.0f, 0.0f, 0.0f, 0.0f}, odd = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int t = 0; t < 16; ++t)
-                acc[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[t], xs[col + 16 * t], acc[k], 0, 0, 0);
+            for (int t = 0; t < 16; t += 2) {
+                even = __builtin_amdgcn_mfma_f32_4x4x1f32(A[t], xs[col + 16 * t], even, 0, 0, 0);
+                odd = __builtin_amdgcn_mfma_f32_4x4x1f32(A[t + 1], xs[col + 16 * t + 16], odd, 0, 0, 0);
+            }
+            acc[k] += even + odd;
         }
     }
     // Lane j + 4 b holds block b's sums for lag j, patterns 0..3.
@@ -881,14 +890,14 @@ __global__ __launch_bounds__(64, 2) void k_walk_grad(const WGroup* __restrict__ 
 }
 
 // partial[c][chunk][k] = sum over the chunk's weights of psi_k times their
-// correlation (summed over splits).  Weights without an entry are left out,
+// correlation (summed over splits), in 64 bits up to the stored sum.  Weights without an entry are left out,
 // whatever their correlation holds.  grid: (kFoldGradChunks, C)
 __global__ __launch_bounds__(256) void k_walk_grad_contract(const PVal* __restrict__ vals,
                                                             const uint8_t* __restrict__ cells,
                                                             const int8_t* __restrict__ cmap,
                                                             const float* __restrict__ corr, float* __restrict__ partial,
                                                             int n, int C, int splits, int chunks, int K) {
-    __shared__ float red[4][kSeparableBasis];
+    __shared__ double red[4][kSeparableBasis];
     __shared__ int map[kCells];
     const int c = blockIdx.y, tid = threadIdx.x;
     if (tid < kCells) {  // four basis functions per cell, a byte each
@@ -897,21 +906,21 @@ __global__ __launch_bounds__(256) void k_walk_grad_contract(const PVal* __restri
         map[tid] = m;
     }
     __syncthreads();
-    float acc[kSeparableBasis];
+    double acc[kSeparableBasis];
 #pragma unroll
-    for (int k = 0; k < kSeparableBasis; ++k) acc[k] = 0.0f;
+    for (int k = 0; k < kSeparableBasis; ++k) acc[k] = 0.0;
     for (int i = blockIdx.x * 256 + tid; i < n; i += kFoldGradChunks * 256) {
         const PVal v = vals[i];
         if (v.v[0] == 0.0f && v.v[1] == 0.0f && v.v[2] == 0.0f && v.v[3] == 0.0f) continue;
-        float s = 0.0f;
+        double s = 0.0;
         for (int sp = 0; sp < splits; ++sp) s += corr[((int64_t)sp * C + c) * n + i];
         const int m = map[cells[i]];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int kj = (m >> (8 * j)) & 255;
-            const float p = v.v[j] * s;
+            const double p = v.v[j] * s;
 #pragma unroll
-            for (int k = 0; k < kSeparableBasis; ++k) acc[k] += kj == k ? p : 0.0f;
+            for (int k = 0; k < kSeparableBasis; ++k) acc[k] += kj == k ? p : 0.0;
         }
     }
 #pragma unroll
@@ -922,7 +931,8 @@ __global__ __launch_bounds__(256) void k_walk_grad_contract(const PVal* __restri
     }
     __syncthreads();
     if (tid < K)
-        partial[((int64_t)c * chunks + blockIdx.x) * K + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+        partial[((int64_t)c * chunks + blockIdx.x) * K + tid] =
+            (float)(red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
 }
 
 template <typename T>

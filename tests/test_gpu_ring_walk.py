@@ -180,3 +180,35 @@ def test_cutoffs_below_the_ring_spacing(case, basis, monkeypatch):
     if not ref.any():
         assert not to_numpy(y).any() and not to_numpy(dw).any() and not to_numpy(dx).any()
     plan.close()
+
+
+@pytest.mark.parametrize("basis", list(K))
+def test_correlated_weight_gradient_rounding(basis, monkeypatch):
+    """The gradient's error against 64 bits when a wave adds up many (batch
+    item, tile) sums: chains of 8 products and of at most 32 sums, then 64
+    bits.  A chain of n random terms in fp32 is off by about 2^-24 sqrt(n / 6)
+    of its sum: 2^-24 sqrt(40 / 6) = 1.5e-7, with the products' and the stored
+    psi's own rounding (2^-24 / sqrt(3) each) 1.7e-7, over enough channels that
+    the figure is not that of a few sums (one chain over the 512 products of a
+    weight: 3.0e-7)."""
+    import oracle
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "128")  # the default; lifts the lines on sizes
+    B, C, a, b = 16, 128 if basis == "separable4x4" else 160, 64, 512
+    tc = 1.5 * math.pi / a
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(76)
+    x, dy = (torch.randn((B, C, a, b), generator=g, device="cuda:0") for _ in range(2))
+    w = torch.zeros((C, K[basis]), device="cuda:0")
+    say("dW rounding", basis)
+    plan = disco.Plan(a, b, a, b, tc, basis=basis, backward=True)
+    _, dw = disco.forward_depthwise_backward(plan, x, w, dy, want_dx=False)
+    got, ref = [], []
+    for ch in range(0, C, 3):
+        xc, dc = (to_numpy(t[:, ch:ch + 1]) for t in (x, dy))
+        ref.append(oracle.default().weight_grad(a, b, a, b, tc, xc, dc, basis=list(K).index(basis))[0, 0])
+        got.append(to_numpy(dw[ch]))
+    err = rel_l2(np.stack(got), np.stack(ref))
+    say("  rel_l2 %.3e" % err)
+    assert err <= 1.7e-7
+    plan.close()
