@@ -172,13 +172,26 @@ int fused_target_entries(const HostOp& h, int tile) {
     return kTargetEntries;
 }
 
-// Output rings with at least this many entries take the spectral path
-// (environment DISCO_SPECTRAL_MIN_ENTRIES overrides, for tuning).
-int spectral_min_entries() {
+// Output rings with at least this many entries are wide: they take the spectral
+// path (environment DISCO_SPECTRAL_MIN_ENTRIES overrides, for tuning).  A direct
+// sum feeds all nine functions of the 3x3 basis.  The other bases, whose tables
+// have up to 16 rows and whose direct sums feed one folded filter, draw the
+// line higher where the ring walk still holds the windows (up to about five
+// rings of cutoff), else at the same place.  2048 x 4096, 8 separable depthwise
+// channels, at 128 and 192 (the spectral rings on the caller's stream):
+// three rings of cutoff 306 us with 104 MB of tables and 313 us with 70 MB,
+// five 580 us with 547 MB and 516 us with 349 MB; six 847 us with 1054 MB and,
+// without a walk, 2242 us; without the tables 677, 1247 and 1858 us.
+constexpr int kWideEntries = 128, kWideEntriesFolded = 192;
+int spectral_min_entries(int basis) {
     const char* v = std::getenv("DISCO_SPECTRAL_MIN_ENTRIES");
     if (v && *v) return std::max(1, std::atoi(v));
-    return 128;
+    return basis == DISCO_BASIS_BILINEAR_3X3 ? kWideEntries : kWideEntriesFolded;
 }
+
+// The most that one op's tables may take (bases other than 3x3): the largest
+// that have been seen to pay, six rings of cutoff at 2048 x 4096.
+constexpr int64_t kFoldTableBytes = (int64_t)1 << 30;
 
 // The environment variable above also lifts the lines on sizes below which
 // the spectral, walk and correlation paths are left to the direct kernels.
@@ -475,11 +488,36 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
     // axisymmetric and separable bases, depthwise calls of any basis): the
     // general one on the packed layout, the blocked one when the longitude
     // stride is 1.  The spectral and sweep layouts are built for the 3x3 basis.
-    std::vector<uint8_t> heavy;
+    const bool grid3 = h.basis == DISCO_BASIS_BILINEAR_3X3;
+    std::vector<uint8_t> heavy((size_t)h.g.n_patterns(), 0);
     std::string err;
     int rc = DISCO_OK;
-    if (spectral_pays(h)) rc = build_spectral(h, spectral_min_entries(), &T->sp, &heavy, &err, true);
-    else heavy.assign((size_t)h.g.n_patterns(), 0);
+    // The rings with wide windows: the spectral ones of the 3x3 basis; of the
+    // others, those left out of the ring walk, at the first line that leaves
+    // it narrow enough.
+    int line = spectral_min_entries(h.basis);
+    if (h.g.stride == 1) {
+        std::vector<uint8_t> wide = wide_patterns(h, line);
+        if ((rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
+        if (T->walk.steps.empty() && line > kWideEntries && !lines_lifted()) {
+            line = kWideEntries;
+            wide = wide_patterns(h, line);
+            if ((rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
+        }
+        if ((s = pack_stencil_host(h, wide, &T->stencil)) != DISCO_OK) return s;
+        T->has_stencil = true;
+        T->bytes[3] = stencil_bytes(T->stencil) + walk_bytes(T->walk);
+        d->has_walk = !T->walk.steps.empty();
+        std::vector<uint8_t> narrow(wide.size());
+        for (size_t i = 0; i < wide.size(); ++i) {
+            narrow[i] = !wide[i];
+            if (wide[i]) d->n_entries_wide += h.pat_ptr[i + 1] - h.pat_ptr[i];
+        }
+        if (d->has_walk) d->work_walk = pattern_work(h, narrow);
+    }
+    // The other bases read the tables beside the walk only (fold_spectral).
+    if (grid3 ? spectral_pays(h) : d->has_walk)
+        rc = build_spectral(h, line, &T->sp, &heavy, &err, true, grid3 ? 0 : kFoldTableBytes);
     if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
     d->n_heavy_rings = (int32_t)T->sp.rings.size();
     int64_t core = 0;
@@ -493,26 +531,10 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
     } else {
         d->work_light = d->work_all;
     }
-    if (h.g.stride == 1) {
-        // The wide patterns are the spectral rings, where the op has them.
-        const std::vector<uint8_t> wide = wide_patterns(h, spectral_min_entries());
-        if ((s = pack_stencil_host(h, wide, &T->stencil)) != DISCO_OK) return s;
-        rc = pack_walk(h, wide, &T->walk, &err);
-        if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
-        T->has_stencil = true;
-        T->bytes[3] = stencil_bytes(T->stencil) + walk_bytes(T->walk);
-        d->has_walk = !T->walk.steps.empty();
-        std::vector<uint8_t> narrow(wide.size());
-        for (size_t i = 0; i < wide.size(); ++i) {
-            narrow[i] = !wide[i];
-            if (wide[i]) d->n_entries_wide += h.pat_ptr[i + 1] - h.pat_ptr[i];
-        }
-        if (d->has_walk) d->work_walk = pattern_work(h, narrow);
-    }
     const CellMap cm = cell_map(h.basis);
     std::vector<int8_t> cmv(&cm.k[0][0], &cm.k[0][0] + sizeof(cm.k));
     if ((s = upload_vec(cmv, &d->cmap_dev, &d->bytes, "hipMalloc(cell map)")) != DISCO_OK) return s;
-    if (h.basis != DISCO_BASIS_BILINEAR_3X3) {
+    if (!grid3) {
         T->bytes[0] = core;
         d->tables = T;
         if (d->n_heavy_rings == 0) d->built.store(kPartCore);  // the group is the spectral tables only

@@ -376,15 +376,15 @@ struct SpectralHost {
     std::vector<float> vs;            // [table][nv][M + 1], scaled by 1 / N
     std::vector<float> tw;            // [N / 2][2]: exp(-2 pi i t / N)
 };
-// Fills *sp (possibly with no rings) and marks heavy patterns in *heavy: the
-// rings whose outputs read at least min_entries (times stride^2) inputs on average, when both
-// ring lengths are powers of two from 64 to 8192.  Ops with several
-// longitude phases are covered only with `phases`.
-// The patterns of the rings with at least that many entries, whatever the
-// ring lengths.
+// The patterns of the wide rings: those whose outputs read at least
+// min_entries (times stride^2) inputs on average, whatever the ring lengths.
 std::vector<uint8_t> wide_patterns(const HostOp& op, int min_entries);
+// Fills *sp (possibly with no rings) and marks its patterns in *heavy: the wide
+// rings, when both ring lengths are powers of two from 64 to 8192 and the
+// tables take at most max_table_bytes (0: any number).  Ops with several
+// longitude phases are covered only with `phases`.
 int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vector<uint8_t>* heavy,
-                   std::string* err, bool phases = false);
+                   std::string* err, bool phases = false, int64_t max_table_bytes = 0);
 
 struct SpectralDev {
     int N = 0, M = 0;            // the finer ring length and its half: tables, twiddles

@@ -88,7 +88,7 @@ std::vector<uint8_t> wide_patterns(const HostOp& op, int min_entries) {
 }
 
 int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vector<uint8_t>* heavy,
-                   std::string* err, bool phases) {
+                   std::string* err, bool phases, int64_t max_table_bytes) {
     (void)err;
     const OpGeom& g = op.g;
     heavy->assign((size_t)g.n_patterns(), 0);
@@ -188,7 +188,6 @@ int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vec
         sp->pair_slot.push_back(sl);
         if (p + 1 == pe.size() || pe[p + 1].to != pe[p].to) sp->pair_ptr.push_back((int32_t)p + 1);
     }
-    *heavy = wide;
     // The table each pair reads: its own, or (bit 31) the equator mirror's
     // with its rows exchanged.
     const size_t n_pairs = pe.size();
@@ -226,6 +225,11 @@ int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vec
             owners.push_back((int32_t)p);
         }
     }
+    if (max_table_bytes > 0 && (int64_t)(owners.size() * (size_t)K * (size_t)(M + 1) * sizeof(float)) > max_table_bytes) {
+        *sp = SpectralHost{};
+        return DISCO_OK;
+    }
+    *heavy = wide;
     // Vhat per table, scaled by 1/N (the inverse transform on the device is
     // unnormalised).  Two real sequences per complex FFT, the tables shared
     // out over a few host threads.
