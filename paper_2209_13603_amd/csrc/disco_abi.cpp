@@ -738,6 +738,24 @@ bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, 
     return fold_walk(op, items, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
            (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || lines_lifted());
 }
+// From 2^25 outputs on those launches run on the plan's helper stream beside the
+// walk (2048 x 4096, 8 separable channels: 313 us on one stream, 273 us beside
+// it; 2049 x 4096, one axisymmetric item, 75 and 87 us).  The helper stream of a
+// 3x3 plan may be in a capture of the fused schedule while another thread
+// makes a depthwise call, which used no stream but its own below those
+// lines and keeps to it; so does a call that is itself captured.
+constexpr int64_t kFoldForkPixels = 1 << 25;
+bool fold_fork(const DeviceOp& op, int64_t items) {
+    return op.basis != DISCO_BASIS_BILINEAR_3X3 && items * op.g.nlat_o * op.g.nlon_o >= kFoldForkPixels;
+}
+// Whether the stream is being captured (the legacy default stream cannot be
+// asked while another one is).
+bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
 // Items assumed where a call is not at hand (work figures): one of the
 // axisymmetric basis (App. B's layer), a depthwise call's of the others.
 int64_t typical_items(const DeviceOp& op) { return op.basis == DISCO_BASIS_AXISYMMETRIC_4 ? 1 : 32; }
@@ -984,8 +1002,11 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
                                            "(16 bytes) and y (4 bytes)");
     // The heavy rings of a folded-weight call through the spectral path (the
     // fused schedule's own are dispatch()'s).
+    // Tables that are not on the device yet cannot be put there under capture:
+    // the blocked kernel, which small calls have put there, sums these rings.
     bool heavy_spectral = axisym && fold_spectral(op, algo, B, Ci, Co);
-    if (ext && heavy_spectral && !(op.built & kPartCore)) heavy_spectral = false;
+    const bool capturing = heavy_spectral && is_capturing(stream);
+    if ((ext || capturing) && !(op.built & kPartCore)) heavy_spectral = false;
     if (mfma) algo = DISCO_ALGO_MATRIX_CORE;
     if (!mfma) {
         algo = resolve_auto(op, algo, Co);
@@ -1069,9 +1090,10 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     // The spectral rings (input transforms, products, inverse transforms) run
     // on the plan's helper stream, forked from and joined back into the
     // caller's stream, beside the direct kernels on the caller's stream; with
-    // the caller's scratch (ext) they run on its own stream instead.
+    // the caller's scratch (ext) they run on its own stream instead, as do
+    // those of folded-weight calls that fold_fork does not send there.
     hipEvent_t fork = nullptr, join = nullptr;
-    const bool fork_aux = (spectral || heavy_spectral) && plan->aux && !ext &&
+    const bool fork_aux = (spectral || (heavy_spectral && !capturing && fold_fork(op, B))) && plan->aux && !ext &&
                           algo != DISCO_ALGO_GATHER_THEN_CONTRACT;
     ExecArgs as = a;
     auto spectral_rings = [&] {
@@ -1270,9 +1292,9 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
                      B * C_x * op.g.nlat_o * op.g.nlon_o < kFoldWalkPixels;
     const bool folded = (depthwise || (op.basis != DISCO_BASIS_BILINEAR_3X3 && C_x == 1 && C_dy == 1)) && op.has_walk &&
                         (op.n_entries_wide == 0 || op.n_heavy_rings > 0) && !few;
-    if (folded) {
-        const int parts = kPartStencil | (op.n_heavy_rings > 0 ? kPartCore : 0);
-        if ((s = ensure_parts(plan, op, parts)) != DISCO_OK) return s;
+    const int folded_parts = kPartStencil | (op.n_heavy_rings > 0 ? kPartCore : 0);
+    if (folded && !((folded_parts & ~op.built) && is_capturing(ds))) {
+        if ((s = ensure_parts(plan, op, folded_parts)) != DISCO_OK) return s;
         ExecArgs fa{};
         fa.op = &op; fa.x = x->data; fa.dy = dy->data; fa.dw = dw->data; fa.dtype = x->dtype;
         fa.B = (int)(B * C_x); fa.Ci = fa.Co = 1; fa.dw_c = (int)C_x; fa.stream = ds; fa.walk = true;
