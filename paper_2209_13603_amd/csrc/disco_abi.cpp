@@ -208,10 +208,21 @@ bool lines_lifted() {
 // from 256 x 512 302 and 278 us; 32 -> 32 channels 192 and 234, 792 and 701 us).
 // The other bases use the tables on one-channel items only (fold_spectral).
 constexpr int64_t kTwoLengthPixels = 1 << 19;
+// Where the spectral rings cannot run on a helper stream beside the direct ones
+// (a caller's scratch, a capture) they pay from 2^21 pixels on, or beside
+// the ring sweep: one after the other and the general kernel alone, 512 x 1024
+// -> 256 x 512 417 and 446 us at twice these sizes, 314 and 263 us at
+// these; 512 x 1024 from 256 x 512, 16 channels, 329 and 304 us, 8 channels with
+// the sweep 94 and 133 us.  The input gradient of a halving layer (a doubling
+// op) beside the weight gradient's pass, which the three streams delay: 16
+// channels 2459 us with them, 2233 without, 4 channels at twice the sizes
+// 3266 and 3321 us.
+constexpr int64_t kTwoLengthAlonePixels = 1 << 21;
+int64_t larger_grid(const OpGeom& g) { return std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o); }
+bool two_lengths(const OpGeom& g) { return g.P > 1 || g.stride > 1; }
 bool spectral_pays(const HostOp& h) {
     const OpGeom& g = h.g;
-    if (h.basis != DISCO_BASIS_BILINEAR_3X3 || (g.P == 1 && g.stride == 1) || lines_lifted()) return true;
-    return std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o) >= kTwoLengthPixels;
+    return h.basis != DISCO_BASIS_BILINEAR_3X3 || !two_lengths(g) || lines_lifted() || larger_grid(g) >= kTwoLengthPixels;
 }
 
 disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
@@ -807,10 +818,11 @@ struct ExtScratch {
 };
 
 // depthwise: x [B, C, ...], w [C, K], y [B, C, ...] (channel c filtered by
-// w[c] alone); algo is then ignored.
+// w[c] alone); algo is then ignored.  beside: the weight gradient's pass runs
+// beside this call (an input gradient).
 disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, const disco_tensor_t* x,
                       const disco_tensor_t* w, disco_tensor_t* y, hipStream_t stream, int32_t algo,
-                      bool depthwise = false, const ExtScratch* ext = nullptr);
+                      bool depthwise = false, const ExtScratch* ext = nullptr, bool beside = false);
 
 disco_status_t run(disco_plan_t plan, const disco_tensor_t* x, const disco_tensor_t* w,
                    disco_tensor_t* y, hipStream_t stream, int32_t algo, bool transpose, bool depthwise = false) {
@@ -967,7 +979,7 @@ int needed_parts(const DeviceOp& op, int32_t algo, bool folded) {
 
 disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, const disco_tensor_t* x,
                       const disco_tensor_t* w, disco_tensor_t* y, hipStream_t stream, int32_t algo,
-                      bool depthwise, const ExtScratch* ext) {
+                      bool depthwise, const ExtScratch* ext, bool beside) {
     disco_status_t s = depthwise ? check_dw_args(plan, op, x, w, y) : check_op_args(plan, op, transpose, x, w, y, algo);
     if (s != DISCO_OK) return s;
     int64_t B = x->shape[0], Ci = x->shape[1], Co = y->shape[1];
@@ -1005,11 +1017,18 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     // Tables that are not on the device yet cannot be put there under capture:
     // the blocked kernel, which small calls have put there, sums these rings.
     bool heavy_spectral = axisym && fold_spectral(op, algo, B, Ci, Co);
-    const bool capturing = heavy_spectral && is_capturing(stream);
+    const bool two_len = !axisym && !mfma && two_lengths(op.g) && op.n_heavy_rings > 0;
+    const bool capturing = (heavy_spectral || two_len) && !ext && is_capturing(stream);
     if ((ext || capturing) && !(op.built & kPartCore)) heavy_spectral = false;
     if (mfma) algo = DISCO_ALGO_MATRIX_CORE;
     if (!mfma) {
+        const bool by_auto = algo == DISCO_ALGO_AUTO;
         algo = resolve_auto(op, algo, Co);
+        if (two_len && by_auto && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !lines_lifted()) {
+            const bool alone = ext || capturing;
+            const bool loses = alone ? !dispatch(op, algo, (int)Ci, (int)Co, x->dtype).sweep : beside && op.g.P > 1;
+            if (loses && !(alone && !(op.built & kPartDirect))) algo = DISCO_ALGO_FUSED_DIRECT;
+        }
         const int parts = needed_parts(op, algo, axisym) | (heavy_spectral ? kPartCore : 0);
         if (parts & ~op.built) {
             if (ext)
@@ -1091,9 +1110,11 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     // on the plan's helper stream, forked from and joined back into the
     // caller's stream, beside the direct kernels on the caller's stream; with
     // the caller's scratch (ext) they run on its own stream instead, as do
-    // those of folded-weight calls that fold_fork does not send there.
+    // those of folded-weight calls that fold_fork does not send there and, under
+    // capture, those of folded-weight calls and of ops between two ring lengths
+    // (whose helper stream is then never in a capture).
     hipEvent_t fork = nullptr, join = nullptr;
-    const bool fork_aux = (spectral || (heavy_spectral && !capturing && fold_fork(op, B))) && plan->aux && !ext &&
+    const bool fork_aux = (heavy_spectral ? fold_fork(op, B) : spectral) && plan->aux && !ext && !capturing &&
                           algo != DISCO_ALGO_GATHER_THEN_CONTRACT;
     ExecArgs as = a;
     auto spectral_rings = [&] {
@@ -1271,7 +1292,8 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
         join.ev = jev;
         ds = plan->aux_dw;
     }
-    if (dx && (s = run_op(plan, adj, !transpose, dy, w, dx, stream, DISCO_ALGO_AUTO, depthwise)) != DISCO_OK) return s;
+    if (dx && (s = run_op(plan, adj, !transpose, dy, w, dx, stream, DISCO_ALGO_AUTO, depthwise, nullptr, ds != stream)) != DISCO_OK)
+        return s;
     if (!dw) return ok();
     int cur = 0;
     if (hipGetDevice(&cur) != hipSuccess) return fail(DISCO_ERR_DEVICE, "hipGetDevice failed");

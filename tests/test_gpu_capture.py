@@ -1,7 +1,9 @@
-"""Calls under stream capture: folded-weight calls past the lines on sizes keep
-to the captured stream, so that another thread's call on the same plan
-goes on; tables that are not on the device yet are not put there under
-capture.  Every replay, with eager work between them, equals the eager result
+"""Calls under stream capture: folded-weight calls past the lines on sizes and
+ops between two ring lengths keep to the captured stream, so that another
+thread's call on the same plan goes on; tables that are not on the device
+yet are not put there under capture.  Where ops between two ring lengths have
+no helper stream, or share the GPU with the weight gradient's pass, they take
+the direct kernels that are faster there.  Every replay, with eager work between them, equals the eager result
 to the rounding of the kernels' different sums.
 """
 import math
@@ -104,4 +106,66 @@ def test_first_large_call_under_capture_needs_no_upload():
     torch.cuda.synchronize()
     assert plan.info()["psi_bytes"] > held and _rel(y, ref) <= 1e-6
     del graph
+    plan.close()
+
+
+def _kernels(run):
+    import torch
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    out = run()
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read(32)
+    disco.kernel_timing(False)
+    return out, set(ran)
+
+
+@pytest.mark.parametrize("chans,grids,alone", [
+    (16, (512, 1024, 256, 512), "direct"),      # halving
+    (16, (256, 512, 512, 1024), "direct"),      # doubling
+    (8, (256, 512, 512, 1024), "spectral"),     # doubling, beside the ring sweep
+])
+def test_two_ring_lengths_without_a_helper_stream(chans, grids, alone):
+    import torch
+    plan = disco.Plan(*grids, 3 * math.pi / min(grids[0], grids[2]))
+    x, w = synth.random_inputs(93, (1, chans) + grids[:2], (chans, chans, 9))
+    xt, wt = torch_dev(x), torch_dev(w)
+    ref, ran = _kernels(lambda: plan.forward(xt, wt))
+    say("two ring lengths", chans, grids, sorted(ran))
+    assert "spectral_mac" in ran
+    y = torch.empty_like(ref)
+    _, ran = _kernels(lambda: plan.forward_noalloc(xt, wt, y))
+    assert ("spectral_mac" in ran) == (alone == "spectral")
+    assert _rel(y, ref) <= 1e-6
+    y2, second = torch.empty_like(ref), torch.cuda.Stream()
+
+    def eager():
+        with torch.cuda.stream(second):
+            plan.forward(xt, wt, y=y2)
+        second.synchronize()
+
+    graph = _capture(lambda: plan.forward(xt, wt, y=y), eager)
+    for _ in range(3):
+        y.zero_()
+        plan.forward(xt, wt, y=y2)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _rel(y, ref) <= 1e-6 and _rel(y2, ref) <= 1e-6
+    del graph
+    plan.close()
+
+
+def test_input_gradient_of_a_halving_layer_beside_its_weight_gradient():
+    import torch
+    plan = disco.Plan(512, 1024, 256, 512, 3 * math.pi / 256, backward=True)
+    x, w = synth.random_inputs(94, (1, 4, 512, 1024), (6, 4, 9))
+    dy = torch.randn((1, 6, 256, 512), device="cuda:0")
+    xt, wt = torch_dev(x), torch_dev(w)
+    (dx0, _), ran = _kernels(lambda: disco.forward_backward(plan, xt, wt, dy, want_dw=False))
+    assert "spectral_mac" in ran
+    (dx1, _), ran = _kernels(lambda: disco.forward_backward(plan, xt, wt, dy))
+    assert "spectral_mac" not in ran
+    say("halving layer's gradients", sorted(ran), _rel(dx1, dx0))
+    assert _rel(dx1, dx0) <= 1e-6
     plan.close()
