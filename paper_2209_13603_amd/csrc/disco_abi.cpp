@@ -1077,14 +1077,19 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     workspace();
     if (ext && ws > ext->bytes) {
         // The direct kernels need less: folded-weight and two-ring-length ops
-        // run them when the transforms do not fit.
+        // run them when the transforms do not fit, and the blocked kernel for
+        // every ring when the walk's folded weights do not either.
         if (heavy_spectral) {
             heavy_spectral = false;
             workspace();
-        } else if (!mfma && !axisym && spectral && (op.g.P > 1 || op.g.stride > 1) && (op.built & kPartDirect)) {
+        } else if (!mfma && !axisym && spectral && two_lengths(op.g) && (op.built & kPartDirect)) {
             algo = DISCO_ALGO_FUSED_DIRECT;
             spectral = sweep = false;
             packed_set = &op.packed;
+            workspace();
+        }
+        if (ws > ext->bytes && a.walk) {
+            a.walk = false;
             workspace();
         }
     }

@@ -212,3 +212,39 @@ def test_correlated_weight_gradient_rounding(basis, monkeypatch):
     say("  rel_l2 %.3e" % err)
     assert err <= 1.7e-7
     plan.close()
+
+
+def test_noalloc_scratch_limit_without_the_walk():
+    """The largest batch whose blocked kernel's partial outputs fit the
+    non-allocating entry point's scratch is accepted, though the walk's folded
+    weights would not fit beside them."""
+    import re
+    import torch
+    L = 180  # no power of two: no spectral rings
+    w = torch_dev(np.random.default_rng(77).standard_normal((1, 1, 4)))
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(77)
+    limit = 64 << 20
+
+    def need(plan, B):
+        x = torch.empty((B, 1, L + 1, 2 * L), device="cuda:0")
+        with pytest.raises(disco.DiscoError) as e:
+            plan.forward_noalloc(x, w, torch.empty_like(x))
+        return int(re.search(r"needs (\d+) bytes", e.value.message).group(1))
+
+    # Of several cutoffs the one whose largest batch leaves least of the scratch.
+    best = None
+    for rings in (2.5, 2.75, 3.0, 3.25, 3.5, 3.75, 4.0, 4.25):
+        plan = disco.Plan(L + 1, 2 * L, L + 1, 2 * L, rings * math.pi / L, basis="axisym4", sampling="poles")
+        per_item = need(plan, 3001) - need(plan, 3000)
+        if best is None or limit % per_item < best[0]:
+            best = (limit % per_item, limit // per_item, plan)
+    left, B, plan = best
+    say("noalloc limit: %d items, %d bytes left" % (B, left))
+    assert left < 64 * 1024
+    x = torch.randn((B, 1, L + 1, 2 * L), generator=g, device="cuda:0")
+    y = plan.forward_noalloc(x, w, torch.empty_like(x))
+    for b in (0, B - 1):
+        one = plan.forward(x[b:b + 1].contiguous(), w)
+        assert rel_l2(to_numpy(y[b]), to_numpy(one[0])) <= 1e-6
+    plan.close()
