@@ -107,7 +107,7 @@ disco_status_t resolve_params(int nlat_in, int nlon_in, int nlat_out, int nlon_o
         return fail(DISCO_ERR_INVALID_ARGUMENT, "theta_c must lie in (0, pi]");
     disco_basis_t b{DISCO_BASIS_BILINEAR_3X3, DISCO_QUAD_SAMPLING_THEOREM, 0.0, DISCO_SAMPLING_CELL_CENTRED, 0};
     if (basis) b = *basis;
-    if ((b.flags & ~(DISCO_PLAN_BACKWARD | DISCO_PLAN_EAGER)) != 0)
+    if ((b.flags & ~(DISCO_PLAN_BACKWARD | DISCO_PLAN_EAGER | DISCO_PLAN_DIRECT)) != 0)
         return fail(DISCO_ERR_INVALID_ARGUMENT, "unknown basis.flags bits");
     if (b.kind != DISCO_BASIS_BILINEAR_3X3 && b.kind != DISCO_BASIS_AXISYMMETRIC_4 &&
         b.kind != DISCO_BASIS_SEPARABLE_4X4)
@@ -474,7 +474,8 @@ int part_index(int part) { return part == kPartCore ? 0 : part == kPartDirect ? 
 // Host side of one op: every group's tables packed, the op's metadata and
 // work figures set, the cell map uploaded (64 bytes).  Nothing else on the
 // device yet.
-disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
+// direct: DISCO_PLAN_DIRECT, neither spectral rings nor a ring walk.
+disco_status_t prepare_op(const HostOp& h, DeviceOp* d, bool direct) {
     if (fault_inject_alloc()) return fail(DISCO_ERR_OUT_OF_MEMORY, "allocation failure injected (DISCO_FAULT_INJECT=alloc)");
     d->g = h.g;
     d->basis = h.basis;
@@ -509,8 +510,8 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
     int line = spectral_min_entries(h.basis);
     if (h.g.stride == 1) {
         std::vector<uint8_t> wide = wide_patterns(h, line);
-        if ((rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
-        if (T->walk.steps.empty() && line > kWideEntries && !lines_lifted()) {
+        if (!direct && (rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
+        if (!direct && T->walk.steps.empty() && line > kWideEntries && !lines_lifted()) {
             line = kWideEntries;
             wide = wide_patterns(h, line);
             if ((rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
@@ -527,7 +528,7 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d) {
         if (d->has_walk) d->work_walk = pattern_work(h, narrow);
     }
     // The other bases read the tables beside the walk only (fold_spectral).
-    if (grid3 ? spectral_pays(h) : d->has_walk)
+    if (!direct && (grid3 ? spectral_pays(h) : d->has_walk))
         rc = build_spectral(h, line, &T->sp, &heavy, &err, true, grid3 ? 0 : kFoldTableBytes);
     if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
     d->n_heavy_rings = (int32_t)T->sp.rings.size();
@@ -738,15 +739,16 @@ int32_t resolve_auto(const DeviceOp& op, int32_t algo, int64_t Co) {
 // us).  The spectral path's three launches and fork pay from 2^23 on (256 x
 // 512, 32 items: 59 us without either, 79 us with both; 512 x 1024, 4 items, 42
 // and 74 us, 32 items 188 and 108 us).  DISCO_ALGO_FUSED_DIRECT keeps the
-// direct sums of the wide rings everywhere.
+// blocked kernel for every ring, whatever the number of items, and with it
+// results that are bitwise the same in any batch.
 constexpr int64_t kFoldWalkPixels = 1 << 22, kFoldWalkPixelsManyItems = 1 << 20, kFoldSpectralPixels = 1 << 23;
-bool fold_walk(const DeviceOp& op, int64_t items, int64_t Ci, int64_t Co) {
+bool fold_walk(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
     const int64_t pixels = items * op.g.nlat_o * op.g.nlon_o;
-    return op.has_walk && Ci == 1 && Co == 1 &&
+    return op.has_walk && Ci == 1 && Co == 1 && algo != DISCO_ALGO_FUSED_DIRECT &&
            (pixels >= (items >= 64 ? kFoldWalkPixelsManyItems : kFoldWalkPixels) || lines_lifted());
 }
 bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
-    return fold_walk(op, items, Ci, Co) && op.n_heavy_rings > 0 && algo != DISCO_ALGO_FUSED_DIRECT &&
+    return fold_walk(op, algo, items, Ci, Co) && op.n_heavy_rings > 0 &&
            (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || lines_lifted());
 }
 // From 2^25 outputs on those launches run on the plan's helper stream beside the
@@ -1016,15 +1018,15 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     // fused schedule's own are dispatch()'s).
     // Tables that are not on the device yet cannot be put there under capture:
     // the blocked kernel, which small calls have put there, sums these rings.
-    bool heavy_spectral = axisym && fold_spectral(op, algo, B, Ci, Co);
+    const int32_t asked = algo;
+    bool heavy_spectral = axisym && fold_spectral(op, asked, B, Ci, Co);
     const bool two_len = !axisym && !mfma && two_lengths(op.g) && op.n_heavy_rings > 0;
     const bool capturing = (heavy_spectral || two_len) && !ext && is_capturing(stream);
     if ((ext || capturing) && !(op.built & kPartCore)) heavy_spectral = false;
     if (mfma) algo = DISCO_ALGO_MATRIX_CORE;
     if (!mfma) {
-        const bool by_auto = algo == DISCO_ALGO_AUTO;
         algo = resolve_auto(op, algo, Co);
-        if (two_len && by_auto && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !lines_lifted()) {
+        if (two_len && asked == DISCO_ALGO_AUTO && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !lines_lifted()) {
             const bool alone = ext || capturing;
             const bool loses = alone ? !dispatch(op, algo, (int)Ci, (int)Co, x->dtype).sweep : beside && op.g.P > 1;
             if (loses && !(alone && !(op.built & kPartDirect))) algo = DISCO_ALGO_FUSED_DIRECT;
@@ -1053,7 +1055,7 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     const PackedDev* packed_set = axisym ? &op.packed : dp.packed;
     // One output channel on a stride-1 op takes the blocked stencil kernel.
     const bool blocked = axisym && op.stencil.P.n_items > 0 && Co == 1;
-    a.walk = blocked && fold_walk(op, B, Ci, Co);
+    a.walk = blocked && fold_walk(op, asked, B, Ci, Co);
     size_t ws_spec = 0, ws_sweep = 0, ws = 0;
     auto workspace = [&] {
         ws_spec = heavy_spectral || spectral ? (workspace_bytes_spectral(a) + 255) / 256 * 256 : 0;
@@ -1537,11 +1539,12 @@ disco_status_t disco_plan_create(int nlat_in, int nlon_in, int nlat_out, int nlo
     plan->params = p;
     plan->tr.src_transpose = plan->fwd_adj.src_transpose = true;
     plan->fwd_adj.src_adjoint = plan->tr_adj.src_adjoint = true;
+    const bool direct = (p.flags & DISCO_PLAN_DIRECT) != 0;
     try {
-        s = prepare_op(hf, &plan->fwd);
-        if (s == DISCO_OK) s = prepare_op(ht, &plan->tr);
-        if (s == DISCO_OK && with_backward) s = prepare_op(hfa, &plan->fwd_adj);
-        if (s == DISCO_OK && with_backward) s = prepare_op(hta, &plan->tr_adj);
+        s = prepare_op(hf, &plan->fwd, direct);
+        if (s == DISCO_OK) s = prepare_op(ht, &plan->tr, direct);
+        if (s == DISCO_OK && with_backward) s = prepare_op(hfa, &plan->fwd_adj, direct);
+        if (s == DISCO_OK && with_backward) s = prepare_op(hta, &plan->tr_adj, direct);
     } catch (const std::bad_alloc&) {
         s = fail(DISCO_ERR_OUT_OF_MEMORY, "host allocation failed while packing psi");
     }
@@ -1744,8 +1747,8 @@ disco_status_t disco_kernel_work(disco_plan_t plan, int32_t transpose, int32_t a
             // Folded psi: one value per (output pixel, input pixel) pair.
             const int64_t light = op.n_entries - op.n_entries_wide, nq = op.g.nq;
             const bool blocked = op.stencil.P.n_items > 0 && c_out == 1;
-            const bool walk = blocked && fold_walk(op, typical_items(op), c_in, c_out);
-            const bool heavy = walk && fold_spectral(op, dp.algo, typical_items(op), c_in, c_out);
+            const bool walk = blocked && fold_walk(op, algo, typical_items(op), c_in, c_out);
+            const bool heavy = walk && fold_spectral(op, algo, typical_items(op), c_in, c_out);
             if (heavy) {
                 spectral_rows(op.spectral, &rows);
                 rows[1].w.pairs = op.n_entries_wide * nq;

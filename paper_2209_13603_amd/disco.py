@@ -39,6 +39,7 @@ BASIS_SIZE = {DISCO_BASIS_BILINEAR_3X3: 9, DISCO_BASIS_AXISYMMETRIC_4: 4, DISCO_
 SAMPLINGS = {"cell_centred": DISCO_SAMPLING_CELL_CENTRED, "poles": DISCO_SAMPLING_POLES}
 DISCO_PLAN_BACKWARD = 1
 DISCO_PLAN_EAGER = 2
+DISCO_PLAN_DIRECT = 4
 
 ALGO_AUTO = 0
 ALGO_GATHER_THEN_CONTRACT = 1
@@ -211,15 +212,18 @@ def _stream(stream):
 
 
 class Plan:
-    """A DISCO plan for one (in-grid, out-grid) pair (``disco_plan_create``)."""
+    """A DISCO plan for one (in-grid, out-grid) pair (``disco_plan_create``).
+    ``direct``: sum every ring directly, whatever the call's size, so that outputs
+    do not depend bitwise on their batch (``DISCO_PLAN_DIRECT``)."""
 
     def __init__(self, nlat_in, nlon_in, nlat_out, nlon_out, theta_c, node_spacing=0.0,
                  quadrature=DISCO_QUAD_FEJER1, basis=DISCO_BASIS_BILINEAR_3X3,
-                 sampling=DISCO_SAMPLING_CELL_CENTRED, backward=False, eager=False):
+                 sampling=DISCO_SAMPLING_CELL_CENTRED, backward=False, eager=False, direct=False):
         lib = library()
         h = ctypes.c_void_p()
         b = _basis(node_spacing, quadrature, basis, sampling,
-                   (DISCO_PLAN_BACKWARD if backward else 0) | (DISCO_PLAN_EAGER if eager else 0))
+                   (DISCO_PLAN_BACKWARD if backward else 0) | (DISCO_PLAN_EAGER if eager else 0)
+                   | (DISCO_PLAN_DIRECT if direct else 0))
         _check(lib.disco_plan_create(nlat_in, nlon_in, nlat_out, nlon_out, float(theta_c),
                                      ctypes.byref(b), ctypes.byref(h)))
         self._h = h

@@ -156,6 +156,57 @@ def test_depthwise_equals_one_channel_ops_bitwise(case, op, basis):
     plan.close()
 
 
+@pytest.mark.parametrize("basis", ["axisym4", "separable4x4", "bilinear3x3"])
+@pytest.mark.parametrize("case,op", [((256, 512, 256, 512), "forward"), ((256, 512, 128, 256), "transpose")],
+                         ids=lambda v: v if isinstance(v, str) else "%dx%d_%dx%d" % v)
+def test_direct_plan_is_bitwise_batch_and_shift_invariant(case, op, basis):
+    """A plan of direct sums on a call of 2^23 outputs (without the flag the ring
+    walk and the spectral rings): each channel equals itself alone, in the
+    output and in the input gradient, and longitude shifts by whole pixels
+    commute with the op, all bitwise; it holds no frequency-domain tables."""
+    import torch
+    a, b, c, d = case
+    C = 64
+    plan = disco.Plan(*case, 3 * math.pi / min(a, c), basis=basis, backward=True, direct=True)
+    K = {"axisym4": 4, "separable4x4": 16, "bilinear3x3": 9}[basis]
+    xs, ys = ((1, C, a, b), (1, C, c, d)) if op == "forward" else ((1, C, c, d), (1, C, a, b))
+    x, w = synth.random_inputs(54, xs, (C, K), c_in=1)
+    xt, wt = torch_dev(x), torch_dev(w)
+    dy = torch_dev(synth.random_inputs(55, ys, (C, K))[0])
+    f = plan.forward_depthwise if op == "forward" else plan.transpose_depthwise
+    g = disco.forward_depthwise_backward if op == "forward" else disco.transpose_depthwise_backward
+    y, (dx, dw) = f(xt, wt), g(plan, xt, wt, dy)
+    for ch in (0, C - 1):
+        one = [t[:, ch:ch + 1].contiguous() for t in (xt, dy)] + [wt[ch:ch + 1].contiguous()]
+        assert torch.equal(f(one[0], one[2])[:, 0], y[:, ch])
+        assert torch.equal(g(plan, one[0], one[2], one[1])[0][:, 0], dx[:, ch])
+    s_in, s_out = (3, 3 * d // b) if op == "forward" else (3, 3 * b // d)
+    assert torch.equal(f(torch.roll(xt, s_in, 3).contiguous(), wt), torch.roll(y, s_out, 3))
+    info = plan.info()
+    assert info["bytes_spectral"] == 0 and info["spectral_rings_forward"] == 0
+    say("  direct plan", case, op, basis, "psi_bytes %.1f MB" % (info["psi_bytes"] / 1e6))
+    # The same call with the flag off, to the rounding of the sums.
+    other = disco.Plan(*case, 3 * math.pi / min(a, c), basis=basis)
+    z = other.forward_depthwise(xt, wt) if op == "forward" else other.transpose_depthwise(xt, wt)
+    assert float((z - y).norm() / y.norm()) <= 1e-6
+    plan.close()
+    other.close()
+
+
+def test_fused_direct_does_not_depend_on_the_batch():
+    """One-channel calls of the folded bases with algo fused_direct: an item of a
+    batch past the lines on sizes equals the item alone, bitwise."""
+    import torch
+    n, B = 256, 64
+    plan = disco.Plan(n, 2 * n, n, 2 * n, 3 * math.pi / n, basis="separable4x4")
+    x, w = synth.random_inputs(56, (B, 1, n, 2 * n), (1, 1, 16))
+    xt, wt = torch_dev(x), torch_dev(w)
+    y = plan.forward(xt, wt, algo="fused_direct")
+    for i in (0, B - 1):
+        assert torch.equal(plan.forward(xt[i:i + 1].contiguous(), wt, algo="fused_direct")[0], y[i])
+    plan.close()
+
+
 def test_depthwise_argument_errors():
     a, b = 16, 32
     plan = disco.Plan(a, b, a, b, 3 * math.pi / 16, basis="separable4x4")
