@@ -234,6 +234,8 @@ disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
     if ((s = upload_vec(S.slot_ring, &d->slot_ring, &d->bytes, "hipMalloc(spectral slots)")) != DISCO_OK) return s;
     if ((s = upload_vec(S.vs, &d->vs, &d->bytes, "hipMalloc(spectral psi)")) != DISCO_OK) return s;
     if ((s = upload_vec(S.tw, &d->tw, &d->bytes, "hipMalloc(twiddles)")) != DISCO_OK) return s;
+    if ((s = upload_vec(S.ent_ptr, &d->ent_ptr, &d->bytes, "hipMalloc(spectral entries)")) != DISCO_OK) return s;
+    if ((s = upload_vec(S.ents, &d->ents, &d->bytes, "hipMalloc(spectral entries)")) != DISCO_OK) return s;
     d->N = S.N;
     d->M = S.M;
     d->Mi = S.Ni / 2;
@@ -246,7 +248,7 @@ disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
 }
 
 void free_spectral(SpectralDev* d) {
-    void* ptrs[] = {d->rings, d->pair_ptr, d->pair_slot, d->pair_tab, d->slot_ring, d->vs, d->tw};
+    void* ptrs[] = {d->rings, d->pair_ptr, d->pair_slot, d->pair_tab, d->slot_ring, d->vs, d->tw, d->ent_ptr, d->ents};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     *d = SpectralDev{};
@@ -539,7 +541,8 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d, bool direct) {
         d->work_spectral = pattern_work(h, heavy);
         d->work_light = pattern_work(h, light);
         core += vec_bytes(T->sp.rings) + vec_bytes(T->sp.pair_ptr) + vec_bytes(T->sp.pair_slot) +
-                vec_bytes(T->sp.pair_tab) + vec_bytes(T->sp.slot_ring) + vec_bytes(T->sp.vs) + vec_bytes(T->sp.tw);
+                vec_bytes(T->sp.pair_tab) + vec_bytes(T->sp.slot_ring) + vec_bytes(T->sp.vs) + vec_bytes(T->sp.tw) +
+                vec_bytes(T->sp.ent_ptr) + vec_bytes(T->sp.ents);
     } else {
         d->work_light = d->work_all;
     }

@@ -363,6 +363,11 @@ struct SweepDev {
 // pair, frequency) store K floats (rows listed in disco_spectral_plan.cpp).
 // Pairs mirrored about the equator share one table (rows exchanged), which
 // halves the tables of an op with both polar caps.
+struct RingEntry {
+    int32_t row, d;  // input ring * nlon_i, offset
+    float v[4];      // its cell's values times q
+    int32_t cell;    // CellMap
+};
 struct SpectralHost {
     int Ni = 0, No = 0;               // input and output ring lengths (powers of two)
     int N = 0, M = 0;                 // max(Ni, No) and M = N / 2
@@ -375,6 +380,10 @@ struct SpectralHost {
     std::vector<int32_t> slot_ring;   // input ring of each slot
     std::vector<float> vs;            // [table][nv][M + 1], scaled by 1 / N
     std::vector<float> tw;            // [N / 2][2]: exp(-2 pi i t / N)
+    // The rings' entries, for the direct sums of a ring whose spectrum is not
+    // finite: CSR over (ring, phase).
+    std::vector<int32_t> ent_ptr;
+    std::vector<RingEntry> ents;
 };
 // The patterns of the wide rings: those whose outputs read at least
 // min_entries (times stride^2) inputs on average, whatever the ring lengths.
@@ -397,6 +406,8 @@ struct SpectralDev {
     int32_t* slot_ring = nullptr;
     float* vs = nullptr;
     float* tw = nullptr;
+    int32_t* ent_ptr = nullptr;
+    RingEntry* ents = nullptr;
     int64_t bytes = 0;
 };
 

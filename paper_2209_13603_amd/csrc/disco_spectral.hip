@@ -12,7 +12,10 @@
 //                  real Vhat_{3a+1} (9 stored floats per pair and frequency),
 //   k_spectral_fold: the same for one-channel items, W folded into the
 //                  tables' rows (every basis; depthwise channels),
-//   k_irfft_rings: y of each heavy ring from Yhat (inverse real DFT).
+//   k_irfft_rings: y of each heavy ring from Yhat (inverse real DFT); a ring
+//                  whose Yhat is not finite is summed directly, so that an
+//                  infinity or NaN of x reaches the outputs whose windows hold
+//                  it and no others, as in the direct kernels.
 // When the ring lengths differ (GEO) the longer one carries the tables: an
 // upsampling op reads the input's spectrum repeated, a downsampling op sums
 // the `alias` frequencies that fold onto each output frequency.
@@ -606,12 +609,50 @@ __global__ __launch_bounds__(64) void k_spectral_fold_grad(const int32_t* __rest
     }
 }
 
+// What a ring's direct sums need: its entries (CSR over (ring, phase); none:
+// no direct sums), the cells' basis functions, x and W.
+template <typename T>
+struct RingSums {
+    const int32_t* ptr;
+    const RingEntry* ent;
+    const int8_t* cmap;
+    const T *x, *w;
+    int64_t n_in;
+    int Ci, Co, K, dw_c, P, stride, nlon_i;
+    bool w_trans;
+};
+
+// Ring h of batch item b and output channel co by direct sums, in 64 bits; all
+// threads.  Only for data with infinities or NaN: nothing is staged.
+template <typename T>
+__device__ void ring_direct(const RingSums<T>& R, int h, int b, int co, T* __restrict__ yr, int nlon_o) {
+    for (int o = threadIdx.x; o < nlon_o; o += blockDim.x) {
+        const int q = o / R.P, r = o - q * R.P;
+        const int e0 = R.ptr[h * R.P + r], e1 = R.ptr[h * R.P + r + 1];
+        double acc = 0.0;
+        for (int ci = 0; ci < R.Ci; ++ci) {
+            const T* xr = R.x + ((int64_t)b * R.Ci + ci) * R.n_in;
+            const T* w = R.w + (int64_t)R.K * (R.dw_c > 0 ? b % R.dw_c : R.w_trans ? ci * R.Co + co : co * R.Ci + ci);
+            for (int e = e0; e < e1; ++e) {
+                const RingEntry E = R.ent[e];
+                float f = 0.0f;
+                for (int m = 0; m < 4; ++m) {
+                    const int k = R.cmap[4 * E.cell + m];
+                    if (k >= 0) f = fmaf(load_val(w, k), E.v[m], f);
+                }
+                acc += (double)f * load_val(xr, E.row + (R.stride * q + E.d) % R.nlon_i);
+            }
+        }
+        store_val(yr, o, (float)acc);
+    }
+}
+
 // y[b][co][ring][:] = inverse real DFT of Yhat[h][b][co][:].  grid: (n_rings, B * Co)
 template <typename T>
 __global__ __launch_bounds__(kFftBlock) void k_irfft_rings(const int32_t* __restrict__ rings,
                                                           const float2* __restrict__ yh,
                                                           const float2* __restrict__ tw, T* __restrict__ y,
-                                                          int B, int Co, int nlat_o, int M, int tws) {
+                                                          int B, int Co, int nlat_o, int M, int tws, RingSums<T> R) {
     extern __shared__ float2 sm[];
     float2* a = sm;
     float2* bb = sm + M;
@@ -621,6 +662,7 @@ __global__ __launch_bounds__(kFftBlock) void k_irfft_rings(const int32_t* __rest
     const int b = blockIdx.y / Co, co = blockIdx.y - (blockIdx.y / Co) * Co;
     const float2* Y = yh + (((int64_t)h * B + b) * Co + co) * (M + 1);
     load_twiddles(tw, thi, tlo, M, tws);
+    bool fine = true;
     for (int m0 = threadIdx.x; m0 < M; m0 += kFftBatch * kFftBlock) {
         float2 xm[kFftBatch], xc[kFftBatch], twm[kFftBatch];
 #pragma unroll
@@ -638,14 +680,15 @@ __global__ __launch_bounds__(kFftBlock) void k_irfft_rings(const int32_t* __rest
             if (m < M) {
                 const float2 e = cadd(xm[u], xc[u]);
                 const float2 o = cmul(csub(xm[u], xc[u]), conjf2(twm[u]));
+                fine &= fabsf(e.x) + fabsf(e.y) + fabsf(o.x) + fabsf(o.y) < INFINITY;
                 a[m] = make_float2(e.x - o.y, e.y + o.x);  // e + i o
             }
         }
     }
-    __syncthreads();
-    const float2* z = fft_lds(a, bb, M, thi, tlo, true);
     const int N = 2 * M;
     const int64_t base = (((int64_t)b * Co + co) * nlat_o + rings[h]) * N;
+    if (__syncthreads_or(!fine) && R.ptr) return ring_direct(R, h, b, co, y + base, N);
+    const float2* z = fft_lds(a, bb, M, thi, tlo, true);
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
         const float2 v = z[j];
         store_val(y, base + 2 * j, v.x);
@@ -667,11 +710,16 @@ hipError_t spectral_rfft(const ExecArgs& a, float2* xh) {
 }
 
 template <typename T>
-hipError_t spectral_irfft(const ExecArgs& a, const float2* yh) {
+hipError_t spectral_irfft(const ExecArgs& a, const float2* yh, bool z) {
     const SpectralDev& S = a.op->spectral;
+    const OpGeom& g = a.op->g;
+    // The planes of Z (no W) have none: what reads them sums over a ring anyway.
+    const RingSums<T> R{z ? nullptr : S.ent_ptr, S.ents, a.op->cmap_dev, (const T*)a.x, (const T*)a.w,
+                        (int64_t)g.nlat_i * g.nlon_i, a.Ci, a.Co, basis_size(a.op->basis), a.dw_c, g.P, g.stride,
+                        g.nlon_i, a.w_trans};
     const int tk = timing_begin("spectral_irfft", a.stream);
     hipLaunchKernelGGL((k_irfft_rings<T>), dim3(S.n_rings, a.B * a.Co), dim3(kFftBlock), fft_lds_bytes(S.Mo), a.stream,
-                       S.rings, yh, (const float2*)S.tw, (T*)a.y, a.B, a.Co, a.op->g.nlat_o, S.Mo, S.M / S.Mo);
+                       S.rings, yh, (const float2*)S.tw, (T*)a.y, a.B, a.Co, g.nlat_o, S.Mo, S.M / S.Mo, R);
     timing_end(tk, a.stream);
     return hipGetLastError();
 }
@@ -767,7 +815,7 @@ hipError_t spectral_dispatch(const ExecArgs& a, float* ws, int stages) {
         e = spectral_mac<T>(a, xh, yh, stages);
         timing_end(tk, a.stream);
     }
-    if (e == hipSuccess && (stages & 4)) e = spectral_irfft<T>(a, yh);
+    if (e == hipSuccess && (stages & 4)) e = spectral_irfft<T>(a, yh, (stages & kSpectralZ) != 0);
     return e;
 }
 

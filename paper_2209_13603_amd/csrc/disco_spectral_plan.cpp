@@ -89,7 +89,6 @@ std::vector<uint8_t> wide_patterns(const HostOp& op, int min_entries) {
 
 int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vector<uint8_t>* heavy,
                    std::string* err, bool phases, int64_t max_table_bytes) {
-    (void)err;
     const OpGeom& g = op.g;
     heavy->assign((size_t)g.n_patterns(), 0);
     *sp = SpectralHost{};
@@ -230,6 +229,23 @@ int build_spectral(const HostOp& op, int min_entries, SpectralHost* sp, std::vec
         return DISCO_OK;
     }
     *heavy = wide;
+    sp->ent_ptr.assign(1, 0);
+    for (int32_t to : rings)
+        for (int r = 0; r < g.P; ++r) {
+            for (int32_t e = op.pat_ptr[(size_t)to * g.P + r]; e < op.pat_ptr[(size_t)to * g.P + r + 1]; ++e) {
+                RingEntry E{};
+                int cell = 0;
+                if (!entry_cell_values(op, e, &cell, E.v)) {
+                    if (err) *err = "internal: basis value outside its hat cell";
+                    return DISCO_ERR_DEVICE;
+                }
+                E.row = op.t_in[(size_t)e] * Ni;
+                E.d = op.d[(size_t)e];
+                E.cell = cell;
+                sp->ents.push_back(E);
+            }
+            sp->ent_ptr.push_back((int32_t)sp->ents.size());
+        }
     // Vhat per table, scaled by 1/N (the inverse transform on the device is
     // unnormalised).  Two real sequences per complex FFT, the tables shared
     // out over a few host threads.

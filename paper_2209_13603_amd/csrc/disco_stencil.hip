@@ -427,6 +427,8 @@ hipError_t stencil_blocked_launch(const ExecArgs& a, const StencilDev& S, float*
     return launch_reduce_partials(a, P, partial);
 }
 
+constexpr uint32_t kNoWeight = 0x80000000u;  // -0
+
 // The folded weights of the ring walk: fw[c][i] = sum_m W[c][map[cell][m]]
 // v[m] for every weight i and channel c (one row when dw_c is 0: Ci = Co = 1).
 // grid: (ceil(n / 256), rows)
@@ -445,7 +447,10 @@ __global__ __launch_bounds__(256) void k_fold_weights(const PVal* __restrict__ v
     if (i >= n) return;
     const PVal v = vals[i];
     const float4 t = *(const float4*)(wt + 4 * cells[i]);
-    fw[(int64_t)c * n + i] = t.x * v.v[0] + t.y * v.v[1] + t.z * v.v[2] + t.w * v.v[3];
+    // A weight without an entry is -0, any other zero +0: where inputs are not
+    // finite the walk leaves the former out (kNoWeight).
+    const bool none = v.v[0] == 0.0f && v.v[1] == 0.0f && v.v[2] == 0.0f && v.v[3] == 0.0f;
+    fw[(int64_t)c * n + i] = none ? -0.0f : t.x * v.v[0] + t.y * v.v[1] + t.z * v.v[2] + t.w * v.v[3] + 0.0f;
 }
 
 // Raw buffer access (word 3 of the descriptor for gfx9 raw access): an offset
@@ -599,6 +604,25 @@ __device__ __forceinline__ void walk_pieces(int n, int desc, const float* __rest
     if (i < n) walk_piece_products(A, acc);
 }
 
+// The same sums where a staged input is not finite: the products are taken for
+// the weights that have an entry only, so that an infinity or NaN reaches the
+// outputs whose windows hold it and no others.
+__device__ __forceinline__ void walk_pieces_checked(int n, int desc, const float* __restrict__ wlds,
+                                                    const float* __restrict__ xl, v4f (&acc)[4]) {
+    for (int i = 0; i < n; ++i) {
+        const int piece = __builtin_amdgcn_readlane(desc, i);
+        const float* x = xl + (piece >> 5);
+        for (int j = 0; j < (piece & 31); ++j)
+#pragma unroll
+            for (int r = 0; r < kWalkPats; ++r) {
+                const float w = wlds[kWalkPats * (kWalkLags * i + j) + r];
+                if (__float_as_uint(w) == kNoWeight) continue;
+#pragma unroll
+                for (int o = 0; o < 4; ++o) acc[o][r] = fmaf(w, x[j + o], acc[o][r]);
+            }
+    }
+}
+
 struct WalkArgs {
     int n_steps, run_len, n_runs, n_tiles, n_slots, pitch, n_weights, dw_c, pat_end, back, ahead;
 };
@@ -626,8 +650,15 @@ __device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* 
     auto load_ring = [&](int t, int start, bool on, float4 (&v)[kWalkLoads]) {
         walk_load_ring<T, LOAD>(x, xr, g, q0, t, start, on, pitch, v);
     };
+    uint32_t odd = 0;  // slots with an infinity or NaN (or very large values)
+    static_assert(kWalkMaxFloats / kWalkTile <= 32, "a bit for each slot");
     auto put_ring = [&](int slot, bool on, const float4 (&v)[kWalkLoads]) {
         float4* dst = xs4 + slot * (pitch >> 2) + lane;
+        bool fine = true;
+#pragma unroll
+        for (int k = 0; k < kWalkLoads; ++k)
+            fine &= fabsf(v[k].x) + fabsf(v[k].y) + fabsf(v[k].z) + fabsf(v[k].w) < INFINITY;
+        if (on) odd = (odd & ~(1u << slot)) | (uint32_t)(__ballot(!fine) != 0) << slot;
 #pragma unroll
         for (int k = 0; k < kWalkLoads; ++k)
             if (on && 256 * k + 4 * lane < pitch) {
@@ -686,7 +717,8 @@ __device__ __forceinline__ void walk_run(float4* __restrict__ xs4, const WStep* 
         v4f acc[4];
 #pragma unroll
         for (int o = 0; o < 4; ++o) acc[o] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-        walk_pieces(S.n, desc, wlds + lane, xl, acc);
+        if (odd == 0) walk_pieces(S.n, desc, wlds + lane, xl, acc);
+        else walk_pieces_checked(S.n, desc, wlds, (const float*)xl, acc);
         // Lane l of a product's column block holds its own output column.
         if (VEC && g.P == 2) {
             // The two phases of two output rings, interleaved in memory.
