@@ -207,7 +207,10 @@ typedef struct {
  * With DISCO_LOG=1 in the environment the plan's statistics go to stderr
  * (per op: patterns, stored entries, non-zero triples, the largest window,
  * full-ring windows, compressed psi; then the schedule's structure, device
- * bytes and build time).  This call, the ops and the gradients each run
+ * bytes and build time).  DISCO_SPECTRAL_MIN_ENTRIES=n in the environment draws
+ * the line from which rings are summed through their DFT at n stored entries,
+ * for this plan's calls of every size (for tests and tuning; results change by
+ * rounding only).  This call, the ops and the gradients each run
  * inside a roctx range named after them (rocprofv3 --marker-trace). */
 disco_status_t disco_plan_create(int nlat_in, int nlon_in, int nlat_out, int nlon_out,
                                  double theta_c, const disco_basis_t* basis,

@@ -173,7 +173,10 @@ int fused_target_entries(const HostOp& h, int tile) {
 }
 
 // Output rings with at least this many entries are wide: they take the spectral
-// path (environment DISCO_SPECTRAL_MIN_ENTRIES overrides, for tuning).  A direct
+// path.  Environment DISCO_SPECTRAL_MIN_ENTRIES, read when a plan is created,
+// draws the line elsewhere, for calls of every size: the lines on sizes below
+// which wide rings and the ring walk are left to the direct kernels are lifted
+// for that plan (tests reach every path on small grids that way).  A direct
 // sum feeds all nine functions of the 3x3 basis.  The other bases, whose tables
 // have up to 16 rows and whose direct sums feed one folded filter, draw the
 // line higher where the ring walk still holds the windows (up to about five
@@ -183,22 +186,14 @@ int fused_target_entries(const HostOp& h, int tile) {
 // five 580 us with 547 MB and 516 us with 349 MB; six 847 us with 1054 MB and,
 // without a walk, 2242 us; without the tables 677, 1247 and 1858 us.
 constexpr int kWideEntries = 128, kWideEntriesFolded = 192;
-int spectral_min_entries(int basis) {
+int wide_line_override() {  // 0: none
     const char* v = std::getenv("DISCO_SPECTRAL_MIN_ENTRIES");
-    if (v && *v) return std::max(1, std::atoi(v));
-    return basis == DISCO_BASIS_BILINEAR_3X3 ? kWideEntries : kWideEntriesFolded;
+    return v && *v ? std::max(1, std::atoi(v)) : 0;
 }
 
 // The most that one op's tables may take (bases other than 3x3): the largest
 // that have been seen to pay, six rings of cutoff at 2048 x 4096.
 constexpr int64_t kFoldTableBytes = (int64_t)1 << 30;
-
-// The environment variable above also lifts the lines on sizes below which
-// the spectral, walk and correlation paths are left to the direct kernels.
-bool lines_lifted() {
-    const char* v = std::getenv("DISCO_SPECTRAL_MIN_ENTRIES");
-    return v && *v;
-}
 
 // 3x3 ops between grids of different longitudes take the spectral path from
 // 2^19 pixels of the larger grid on: its products are a chain over input rings
@@ -221,8 +216,7 @@ constexpr int64_t kTwoLengthAlonePixels = 1 << 21;
 int64_t larger_grid(const OpGeom& g) { return std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o); }
 bool two_lengths(const OpGeom& g) { return g.P > 1 || g.stride > 1; }
 bool spectral_pays(const HostOp& h) {
-    const OpGeom& g = h.g;
-    return h.basis != DISCO_BASIS_BILINEAR_3X3 || !two_lengths(g) || lines_lifted() || larger_grid(g) >= kTwoLengthPixels;
+    return h.basis != DISCO_BASIS_BILINEAR_3X3 || !two_lengths(h.g) || larger_grid(h.g) >= kTwoLengthPixels;
 }
 
 disco_status_t upload_spectral(const SpectralHost& S, SpectralDev* d) {
@@ -509,11 +503,13 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d, bool direct) {
     // The rings with wide windows: the spectral ones of the 3x3 basis; of the
     // others, those left out of the ring walk, at the first line that leaves
     // it narrow enough.
-    int line = spectral_min_entries(h.basis);
+    const int override_line = wide_line_override();
+    d->lines_lifted = override_line > 0;
+    int line = d->lines_lifted ? override_line : grid3 ? kWideEntries : kWideEntriesFolded;
     if (h.g.stride == 1) {
         std::vector<uint8_t> wide = wide_patterns(h, line);
         if (!direct && (rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
-        if (!direct && T->walk.steps.empty() && line > kWideEntries && !lines_lifted()) {
+        if (!direct && T->walk.steps.empty() && line > kWideEntries && !d->lines_lifted) {
             line = kWideEntries;
             wide = wide_patterns(h, line);
             if ((rc = pack_walk(h, wide, &T->walk, &err)) != DISCO_OK) return fail((disco_status_t)rc, err);
@@ -530,7 +526,7 @@ disco_status_t prepare_op(const HostOp& h, DeviceOp* d, bool direct) {
         if (d->has_walk) d->work_walk = pattern_work(h, narrow);
     }
     // The other bases read the tables beside the walk only (fold_spectral).
-    if (!direct && (grid3 ? spectral_pays(h) : d->has_walk))
+    if (!direct && (grid3 ? d->lines_lifted || spectral_pays(h) : d->has_walk))
         rc = build_spectral(h, line, &T->sp, &heavy, &err, true, grid3 ? 0 : kFoldTableBytes);
     if (rc != DISCO_OK) return fail((disco_status_t)rc, err);
     d->n_heavy_rings = (int32_t)T->sp.rings.size();
@@ -748,11 +744,11 @@ constexpr int64_t kFoldWalkPixels = 1 << 22, kFoldWalkPixelsManyItems = 1 << 20,
 bool fold_walk(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
     const int64_t pixels = items * op.g.nlat_o * op.g.nlon_o;
     return op.has_walk && Ci == 1 && Co == 1 && algo != DISCO_ALGO_FUSED_DIRECT &&
-           (pixels >= (items >= 64 ? kFoldWalkPixelsManyItems : kFoldWalkPixels) || lines_lifted());
+           (pixels >= (items >= 64 ? kFoldWalkPixelsManyItems : kFoldWalkPixels) || op.lines_lifted);
 }
 bool fold_spectral(const DeviceOp& op, int32_t algo, int64_t items, int64_t Ci, int64_t Co) {
     return fold_walk(op, algo, items, Ci, Co) && op.n_heavy_rings > 0 &&
-           (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || lines_lifted());
+           (items * op.g.nlat_o * op.g.nlon_o >= kFoldSpectralPixels || op.lines_lifted);
 }
 // From 2^25 outputs on those launches run on the plan's helper stream beside the
 // walk (2048 x 4096, 8 separable channels: 313 us on one stream, 273 us beside
@@ -1029,7 +1025,7 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     if (mfma) algo = DISCO_ALGO_MATRIX_CORE;
     if (!mfma) {
         algo = resolve_auto(op, algo, Co);
-        if (two_len && asked == DISCO_ALGO_AUTO && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !lines_lifted()) {
+        if (two_len && asked == DISCO_ALGO_AUTO && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !op.lines_lifted) {
             const bool alone = ext || capturing;
             const bool loses = alone ? !dispatch(op, algo, (int)Ci, (int)Co, x->dtype).sweep : beside && op.g.P > 1;
             if (loses && !(alone && !(op.built & kPartDirect))) algo = DISCO_ALGO_FUSED_DIRECT;
@@ -1320,7 +1316,7 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
     // op's rings are covered by the walk and the spectral tables.
     // The nine sums of the 3x3 basis come from one fp32 sweep and stay the
     // better path below 2^22 pixels (512 x 1024, 4 items: 165 us against 182).
-    const bool few = op.basis == DISCO_BASIS_BILINEAR_3X3 && x->dtype == DISCO_FLOAT32 && !lines_lifted() &&
+    const bool few = op.basis == DISCO_BASIS_BILINEAR_3X3 && x->dtype == DISCO_FLOAT32 && !op.lines_lifted &&
                      B * C_x * op.g.nlat_o * op.g.nlon_o < kFoldWalkPixels;
     const bool folded = (depthwise || (op.basis != DISCO_BASIS_BILINEAR_3X3 && C_x == 1 && C_dy == 1)) && op.has_walk &&
                         (op.n_entries_wide == 0 || op.n_heavy_rings > 0) && !few;

@@ -561,6 +561,7 @@ struct DeviceOp {
     int64_t n_entries = 0;
     int64_t n_entries_wide = 0;   // stride-1 ops: those of the wide patterns
     bool has_walk = false;        // the stencil layout has a ring walk
+    bool lines_lifted = false;    // calls of every size take the walk and the wide rings' path
     int64_t nnz_pairs = 0;
     int64_t bytes = 0;
     int64_t bytes_entries = 0;  // pat_ptr + entries (+ the cell map)

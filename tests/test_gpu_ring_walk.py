@@ -45,7 +45,8 @@ def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis, monkeypatc
     x, w = synth.random_inputs(71, xs, (C, K[basis]), dtype=dtype, c_in=1)
     say("ring walk", case, basis, dtype)
     plan = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp)
-    one = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp)
+    monkeypatch.delenv("DISCO_SPECTRAL_MIN_ENTRIES")
+    one = disco.Plan(a, b, c, d, tc, basis=basis, sampling=smp)  # below the lines
     xt, wt = torch_dev(x, dtype), torch_dev(w, dtype)
     disco.kernel_timing(True)
     disco.kernel_timing_read()
@@ -53,7 +54,6 @@ def test_depthwise_walk_and_spectral_match_direct(case, dtype, basis, monkeypatc
     ran = disco.kernel_timing_read()
     disco.kernel_timing(False)
     assert "stencil_walk" in ran and "spectral_mac" in ran
-    monkeypatch.delenv("DISCO_SPECTRAL_MIN_ENTRIES")  # back below the lines
     for ch in (0, C // 2, C - 1):
         for bi in (0, B - 1):
             xc = xt[bi:bi + 1, ch:ch + 1].contiguous()
@@ -247,4 +247,24 @@ def test_noalloc_scratch_limit_without_the_walk():
     for b in (0, B - 1):
         one = plan.forward(x[b:b + 1].contiguous(), w)
         assert rel_l2(to_numpy(y[b]), to_numpy(one[0])) <= 1e-6
+    plan.close()
+
+
+def test_size_lines_are_a_plans_own(monkeypatch):
+    """The environment variable that lifts the lines on sizes is read when a plan
+    is created; setting it later changes no call."""
+    import torch
+    n = 128
+    x, w = (torch_dev(v) for v in synth.random_inputs(78, (1, 2, n, 2 * n), (2, 16), c_in=1))
+    plan = disco.Plan(n, 2 * n, n, 2 * n, 3 * math.pi / n, basis="separable4x4")
+    y0 = plan.forward_depthwise(x, w)
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "128")
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    y1 = plan.forward_depthwise(x, w)
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    assert "stencil_blocked" in ran and "stencil_walk" not in ran
+    assert torch.equal(y0, y1)
     plan.close()
