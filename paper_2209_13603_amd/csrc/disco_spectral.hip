@@ -10,8 +10,9 @@
 //   k_spectral   : Yhat[co][m] = sum_{t_i, ci} Xhat[t_i][ci][m] sum_k W[co][ci][k]
 //                  conj(Vhat_k[m]), using Vhat_{3a+2} = conj(Vhat_{3a}) and
 //                  real Vhat_{3a+1} (9 stored floats per pair and frequency),
-//   k_spectral_fold: the same for one-channel items, W folded into the
-//                  tables' rows (every basis; depthwise channels),
+//   k_spectral_fold: the same for one-channel items of ops without a longitude
+//                  stride, W folded into the tables' rows (every basis;
+//                  depthwise channels),
 //   k_irfft_rings: y of each heavy ring from Yhat (inverse real DFT); a ring
 //                  whose Yhat is not finite is summed directly, so that an
 //                  infinity or NaN of x reaches the outputs whose windows hold
@@ -452,6 +453,7 @@ template <> struct FoldRows<DISCO_BASIS_SEPARABLE_4X4> {
 // Xhat from L2 or HBM (4 K + 8 CT BT bytes per pair and bin), so fewer items
 // per wave cost more (2048 x 4096, 8 channels: 74 us with eight, 105 us with
 // four, the rings not ordered by XCD).
+// GEO: an upsampling op (the ring walk beside it has no longitude stride).
 // grid: nx H nz (spec_item), nx = ceil((Mo+1)/64), nz = ceil(C / CT) * ceil(B / BT)
 template <typename T, int BASIS, int CT, int BT, bool GEO>
 __global__ __launch_bounds__(64) void k_spectral_fold(const int32_t* __restrict__ pair_ptr,
@@ -486,38 +488,35 @@ __global__ __launch_bounds__(64) void k_spectral_fold(const int32_t* __restrict_
         const int32_t tb = pair_tab[p];
         const float* vt = vs + (int64_t)(tb & 0x7fffffff) * K * vstride;
         const float2* xp = xh + (int64_t)pair_slot[p] * B * C * xstride;
-        for (int al = 0; al < (GEO ? S.alias : 1); ++al) {
-            int mv = m, mx = m;
-            float sv = 1.0f, sx = 1.0f;
-            if constexpr (GEO) spec_bins(S, m, al, &mv, &mx, &sv, &sx);
-            float V[K];
-            float2 X[CT][BT];
+        int mv = m, mx = m;
+        float sv = 1.0f, sx = 1.0f;  // mv = m <= M here, so sv = 1
+        if constexpr (GEO) spec_bins(S, m, 0, &mv, &mx, &sv, &sx);
+        float V[K];
+        float2 X[CT][BT];
 #pragma unroll
-            for (int r = 0; r < K; ++r) V[r] = vt[(tb < 0 ? R::mirror(r) : r) * vstride + mv];
+        for (int r = 0; r < K; ++r) V[r] = vt[(tb < 0 ? R::mirror(r) : r) * vstride + mv];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                for (int bt = 0; bt < BT; ++bt) X[ct][bt] = xp[(int64_t)item(ct, bt) * xstride + mx];
+            for (int bt = 0; bt < BT; ++bt) X[ct][bt] = xp[(int64_t)item(ct, bt) * xstride + mx];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                float fr = 0.0f, fi = 0.0f;
+        for (int ct = 0; ct < CT; ++ct) {
+            float fr = 0.0f, fi = 0.0f;
 #pragma unroll
-                for (int r = 0; r < K; ++r) {
-                    if (R::imag(r)) fi = fmaf(cw[ct * K + r], V[r], fi);
-                    else fr = fmaf(cw[ct * K + r], V[r], fr);
-                }
-                if constexpr (GEO) fi *= sv;
+            for (int r = 0; r < K; ++r) {
+                if (R::imag(r)) fi = fmaf(cw[ct * K + r], V[r], fi);
+                else fr = fmaf(cw[ct * K + r], V[r], fr);
+            }
 #pragma unroll
-                for (int bt = 0; bt < BT; ++bt) {
-                    float2 x = X[ct][bt];
-                    if constexpr (GEO) x.y *= sx;
-                    float2& y = Y[ct][bt];
-                    y.x = fmaf(fr, x.x, y.x);
-                    y.y = fmaf(fr, x.y, y.y);
-                    if constexpr (BASIS != DISCO_BASIS_AXISYMMETRIC_4) {
-                        y.x = fmaf(-fi, x.y, y.x);
-                        y.y = fmaf(fi, x.x, y.y);
-                    }
+            for (int bt = 0; bt < BT; ++bt) {
+                float2 x = X[ct][bt];
+                if constexpr (GEO) x.y *= sx;
+                float2& y = Y[ct][bt];
+                y.x = fmaf(fr, x.x, y.x);
+                y.y = fmaf(fr, x.y, y.y);
+                if constexpr (BASIS != DISCO_BASIS_AXISYMMETRIC_4) {
+                    y.x = fmaf(-fi, x.y, y.x);
+                    y.y = fmaf(fi, x.x, y.y);
                 }
             }
         }
@@ -567,31 +566,28 @@ __global__ __launch_bounds__(64) void k_spectral_fold_grad(const int32_t* __rest
             const float* vt = vs + (int64_t)(tb & 0x7fffffff) * K * vstride;
             const float2* xp = xh + (int64_t)pair_slot[p] * B * C * xstride;
             const float2* dp = dyh + (int64_t)h * B * C * ystride + m;
-            for (int al = 0; al < (GEO ? S.alias : 1); ++al) {
-                int mv = m, mx = m;
-                float sv = 1.0f, sx = 1.0f;
-                if constexpr (GEO) spec_bins(S, m, al, &mv, &mx, &sv, &sx);
-                float V[K];
+            int mv = m, mx = m;
+            float sv = 1.0f, sx = 1.0f;
+            if constexpr (GEO) spec_bins(S, m, 0, &mv, &mx, &sv, &sx);
+            float V[K];
 #pragma unroll
-                for (int r = 0; r < K; ++r) V[r] = on * vt[(tb < 0 ? R::mirror(r) : r) * vstride + mv];
-                float qr[CT], qi[CT];
+            for (int r = 0; r < K; ++r) V[r] = on * vt[(tb < 0 ? R::mirror(r) : r) * vstride + mv];
+            float qr[CT], qi[CT];
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) qr[ct] = qi[ct] = 0.0f;
-                for (int b = 0; b < B; ++b)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) {
-                        const int64_t item = (int64_t)b * C + (c0 + ct < C ? c0 + ct : C - 1);
-                        const float2 X = xp[item * xstride + mx], D = dp[item * ystride];
-                        const float xy = GEO ? sx * X.y : X.y;
-                        qr[ct] = fmaf(X.x, D.x, fmaf(xy, D.y, qr[ct]));
-                        qi[ct] = fmaf(xy, D.x, fmaf(-X.x, D.y, qi[ct]));
-                    }
+            for (int ct = 0; ct < CT; ++ct) qr[ct] = qi[ct] = 0.0f;
+            for (int b = 0; b < B; ++b)
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
-                    if constexpr (GEO) qi[ct] *= sv;
-#pragma unroll
-                    for (int r = 0; r < K; ++r) G[ct][r] = fmaf(V[r], R::imag(r) ? qi[ct] : qr[ct], G[ct][r]);
+                    const int64_t item = (int64_t)b * C + (c0 + ct < C ? c0 + ct : C - 1);
+                    const float2 X = xp[item * xstride + mx], D = dp[item * ystride];
+                    const float xy = GEO ? sx * X.y : X.y;
+                    qr[ct] = fmaf(X.x, D.x, fmaf(xy, D.y, qr[ct]));
+                    qi[ct] = fmaf(xy, D.x, fmaf(-X.x, D.y, qi[ct]));
                 }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+                for (int r = 0; r < K; ++r) G[ct][r] = fmaf(V[r], R::imag(r) ? qi[ct] : qr[ct], G[ct][r]);
             }
         }
     }
