@@ -1079,7 +1079,8 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
     if (ext && ws > ext->bytes) {
         // The direct kernels need less: folded-weight and two-ring-length ops
         // run them when the transforms do not fit, and the blocked kernel for
-        // every ring when the walk's folded weights do not either.
+        // every ring when the walk's folded weights do not either; the
+        // matrix-core kernel's W operands are smaller in narrower tiles.
         if (heavy_spectral) {
             heavy_spectral = false;
             workspace();
@@ -1089,8 +1090,9 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
             packed_set = &op.packed;
             workspace();
         }
-        if (ws > ext->bytes && a.walk) {
+        if (ws > ext->bytes && (a.walk || mfma)) {
             a.walk = false;
+            a.narrow_mfma = true;
             workspace();
         }
     }

@@ -590,6 +590,9 @@ struct ExecArgs {
     // patterns through k_stencil_walk, the others through the blocked kernel
     // (heavy_spectral: the spectral path writes those instead).
     bool walk = false, heavy_spectral = false;
+    // Matrix-core kernel: at most 32 output channels per workgroup (W operands
+    // of fewer padded channels).
+    bool narrow_mfma = false;
     // Weight gradient of one-channel items instead (launch_stencil_blocked):
     // the upstream gradient, laid out as y, and dW [dw_c or 1][K].
     const void* dy = nullptr;

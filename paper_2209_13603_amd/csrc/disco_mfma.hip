@@ -496,10 +496,22 @@ __global__ __launch_bounds__(kMfmaTile, 2) void k_mfma_pair(
     }
 }
 
-int mfma_cob(int Co, int P) { return Co <= 16 ? 1 : Co <= 32 || P > 1 ? 2 : 4; }
+// 16-channel output blocks per workgroup.  64 output channels (one phase) spare
+// a second gather of every input but make half the workgroups, each about 7 %
+// longer; they pay where they leave a CU one workgroup fewer to run.  bf16, 64
+// -> 64 channels, 32 and 64 a workgroup: 32 x 64 sphere 53 and 59 us, 64 x 128 70
+// and 76 us, four items 102 and 85 us; 64 x 128 -> 32 x 64 87 and 92 us, two
+// items 128 and 94 us; 256 x 512, 48 -> 60 channels, 180 and 135 us.
+int mfma_cob(const ExecArgs& a) {
+    if (a.Co <= 16) return 1;
+    const MfmaDev& M = a.op->mfma;
+    const int64_t n = (int64_t)M.n_segs * M.n_qtiles * a.B;
+    const bool wide = n * ((a.Co + 31) / 32) / 256 > n * ((a.Co + 63) / 64) / 256;
+    return a.op->g.P == 1 && wide && !a.narrow_mfma ? 4 : 2;
+}
 int mfma_pairs(int Ci) { return (Ci + kMfmaCis - 1) / kMfmaCis * (kMfmaCis / 2); }
 size_t mfma_wop_bytes(const ExecArgs& a) {
-    const int cob = mfma_cob(a.Co, a.op->g.P), n_cot = (a.Co + 16 * cob - 1) / (16 * cob);
+    const int cob = mfma_cob(a), n_cot = (a.Co + 16 * cob - 1) / (16 * cob);
     return ((size_t)mfma_pairs(a.Ci) * n_cot * cob * 64 * 16 + 255) / 256 * 256;
 }
 
@@ -532,7 +544,7 @@ size_t workspace_bytes_mfma(const ExecArgs& a) {
 hipError_t launch_mfma(const ExecArgs& a, void* ws) {
     const MfmaDev& M = a.op->mfma;
     if (M.n_segs == 0) return hipSuccess;
-    const int cob = mfma_cob(a.Co, a.op->g.P), n_cot = (a.Co + 16 * cob - 1) / (16 * cob);
+    const int cob = mfma_cob(a), n_cot = (a.Co + 16 * cob - 1) / (16 * cob);
     const int n_pairs = mfma_pairs(a.Ci), n_cb = n_cot * cob;
     uint4* wop = (uint4*)ws;
     float* partial = (float*)((char*)ws + mfma_wop_bytes(a));

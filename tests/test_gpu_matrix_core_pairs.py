@@ -13,7 +13,7 @@ import math
 import numpy as np
 import pytest
 
-from gpu_util import rel_l2, run_gpu, run_oracle, say
+from gpu_util import rel_l2, run_gpu, run_oracle, say, torch_dev
 from paper_2209_13603_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +43,25 @@ def test_wide_forms_against_oracle(op, case, chans):
     plan.close()
     assert rel_l2(y, ref) <= 5e-3
     assert float(np.abs(y - ref).max() / np.abs(ref).max()) <= 2e-2
+
+
+@pytest.mark.parametrize("chans", [(20, 40), (8, 64), (33, 96)], ids=lambda c: "%dto%d" % c)
+@pytest.mark.parametrize("case", [(64, 128, 64, 128), (64, 128, 32, 64)], ids=lambda c: "%dx%d_%dx%d" % c)
+def test_output_channels_per_workgroup(case, chans):
+    """32 output channels a workgroup (one item) and 64 (six items) give the same
+    bits, and the oracle's values."""
+    import torch
+    a, b, c, d = case
+    ci, co = chans
+    args = (a, b, c, d, 3 * math.pi / c)
+    x, w = synth.random_inputs(67, (6, ci, a, b), (co, ci, 9), dtype="bf16")
+    say("output channels per workgroup", case, chans)
+    y, plan = run_gpu(args, x, w, "forward", dtype="bf16", algo="matrix_core")
+    xt, wt = torch_dev(x, "bf16"), torch_dev(w, "bf16")
+    six = plan.forward(xt, wt, algo="matrix_core")
+    for i in (0, 5):
+        one = plan.forward(xt[i:i + 1].contiguous(), wt, algo="matrix_core")
+        assert torch.equal(one[0], six[i])
+    ref = run_oracle(args, x[:1], w, "forward")
+    assert rel_l2(y[:1], ref) <= 2e-2
+    plan.close()
