@@ -575,15 +575,26 @@ __global__ __launch_bounds__(64) void k_spectral_fold_grad(const int32_t* __rest
             float qr[CT], qi[CT];
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) qr[ct] = qi[ct] = 0.0f;
-            for (int b = 0; b < B; ++b)
+            // Batch items in chains of sixteen.
+            for (int b0 = 0; b0 < B; b0 += 16) {
+                float cr[CT], ci[CT];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) cr[ct] = ci[ct] = 0.0f;
+                for (int b = b0; b < (b0 + 16 < B ? b0 + 16 : B); ++b)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        const int64_t item = (int64_t)b * C + (c0 + ct < C ? c0 + ct : C - 1);
+                        const float2 X = xp[item * xstride + mx], D = dp[item * ystride];
+                        const float xy = GEO ? sx * X.y : X.y;
+                        cr[ct] = fmaf(X.x, D.x, fmaf(xy, D.y, cr[ct]));
+                        ci[ct] = fmaf(xy, D.x, fmaf(-X.x, D.y, ci[ct]));
+                    }
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
-                    const int64_t item = (int64_t)b * C + (c0 + ct < C ? c0 + ct : C - 1);
-                    const float2 X = xp[item * xstride + mx], D = dp[item * ystride];
-                    const float xy = GEO ? sx * X.y : X.y;
-                    qr[ct] = fmaf(X.x, D.x, fmaf(xy, D.y, qr[ct]));
-                    qi[ct] = fmaf(xy, D.x, fmaf(-X.x, D.y, qi[ct]));
+                    qr[ct] += cr[ct];
+                    qi[ct] += ci[ct];
                 }
+            }
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
 #pragma unroll
