@@ -211,7 +211,7 @@ constexpr int64_t kTwoLengthPixels = 1 << 19;
 // the sweep 94 and 133 us.  The input gradient of a halving layer (a doubling
 // op) beside the weight gradient's pass, which the three streams delay: 16
 // channels 2459 us with them, 2233 without, 4 channels at twice the sizes
-// 3266 and 3321 us.
+// 3266 and 3321 us (and without that pass, so that dx does not depend on it).
 constexpr int64_t kTwoLengthAlonePixels = 1 << 21;
 int64_t larger_grid(const OpGeom& g) { return std::max((int64_t)g.nlat_i * g.nlon_i, (int64_t)g.nlat_o * g.nlon_o); }
 bool two_lengths(const OpGeom& g) { return g.P > 1 || g.stride > 1; }
@@ -819,11 +819,11 @@ struct ExtScratch {
 };
 
 // depthwise: x [B, C, ...], w [C, K], y [B, C, ...] (channel c filtered by
-// w[c] alone); algo is then ignored.  beside: the weight gradient's pass runs
-// beside this call (an input gradient).
+// w[c] alone); algo is then ignored.  input_grad: this is the input gradient of
+// a backward call, which the weight gradient's pass may run beside.
 disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, const disco_tensor_t* x,
                       const disco_tensor_t* w, disco_tensor_t* y, hipStream_t stream, int32_t algo,
-                      bool depthwise = false, const ExtScratch* ext = nullptr, bool beside = false);
+                      bool depthwise = false, const ExtScratch* ext = nullptr, bool input_grad = false);
 
 disco_status_t run(disco_plan_t plan, const disco_tensor_t* x, const disco_tensor_t* w,
                    disco_tensor_t* y, hipStream_t stream, int32_t algo, bool transpose, bool depthwise = false) {
@@ -980,7 +980,7 @@ int needed_parts(const DeviceOp& op, int32_t algo, bool folded) {
 
 disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, const disco_tensor_t* x,
                       const disco_tensor_t* w, disco_tensor_t* y, hipStream_t stream, int32_t algo,
-                      bool depthwise, const ExtScratch* ext, bool beside) {
+                      bool depthwise, const ExtScratch* ext, bool input_grad) {
     disco_status_t s = depthwise ? check_dw_args(plan, op, x, w, y) : check_op_args(plan, op, transpose, x, w, y, algo);
     if (s != DISCO_OK) return s;
     int64_t B = x->shape[0], Ci = x->shape[1], Co = y->shape[1];
@@ -1027,7 +1027,7 @@ disco_status_t run_op(disco_plan_t plan, const DeviceOp& op, bool transpose, con
         algo = resolve_auto(op, algo, Co);
         if (two_len && asked == DISCO_ALGO_AUTO && algo == DISCO_ALGO_FUSED && larger_grid(op.g) < kTwoLengthAlonePixels && !op.lines_lifted) {
             const bool alone = ext || capturing;
-            const bool loses = alone ? !dispatch(op, algo, (int)Ci, (int)Co, x->dtype).sweep : beside && op.g.P > 1;
+            const bool loses = alone ? !dispatch(op, algo, (int)Ci, (int)Co, x->dtype).sweep : input_grad && op.g.P > 1;
             if (loses && !(alone && !(op.built & kPartDirect))) algo = DISCO_ALGO_FUSED_DIRECT;
         }
         const int parts = needed_parts(op, algo, axisym) | (heavy_spectral ? kPartCore : 0);
@@ -1300,7 +1300,7 @@ disco_status_t backward(disco_plan_t plan, bool transpose, const disco_tensor_t*
         join.ev = jev;
         ds = plan->aux_dw;
     }
-    if (dx && (s = run_op(plan, adj, !transpose, dy, w, dx, stream, DISCO_ALGO_AUTO, depthwise, nullptr, ds != stream)) != DISCO_OK)
+    if (dx && (s = run_op(plan, adj, !transpose, dy, w, dx, stream, DISCO_ALGO_AUTO, depthwise, nullptr, true)) != DISCO_OK)
         return s;
     if (!dw) return ok();
     int cur = 0;
