@@ -69,6 +69,41 @@ def main():
     ref = run_oracle(args5, x5, oracle.depthwise_weights(w5.astype(np.float64)), "forward", basis=2)
     check("separable depthwise 32x64 C=3", rel_l2(y, ref), 1e-5)
     plan.close()
+    # The ring walk with spectral and with blocked wide rings, one and two phases,
+    # and the weight gradient over its layout (past the lines on sizes).
+    os.environ["DISCO_SPECTRAL_MIN_ENTRIES"] = "64"
+    for (a6, b6, c6, d6), op in (((64, 128, 64, 128), "forward"), ((60, 450, 60, 450), "forward"),
+                                 ((90, 362, 45, 181), "transpose"), ((64, 256, 32, 128), "transpose")):
+        for dtype in ("fp32", "bf16"):
+            args6 = (a6, b6, c6, d6, (3 if b6 < 6 * a6 else 1.5) * math.pi / min(a6, c6))
+            xs, ys = ((2, 3, a6, b6), (2, 3, c6, d6)) if op == "forward" else ((2, 3, c6, d6), (2, 3, a6, b6))
+            x6, w6 = synth.random_inputs(16, xs, (3, 16), dtype=dtype, c_in=1)
+            dy6 = synth.random_inputs(17, ys, (3, 16), dtype=dtype)[0]
+            plan = disco.Plan(*args6, basis="separable4x4", backward=True)
+            f = plan.forward_depthwise if op == "forward" else plan.transpose_depthwise
+            g = disco.forward_depthwise_backward if op == "forward" else disco.transpose_depthwise_backward
+            disco.kernel_timing(True)
+            disco.kernel_timing_read()
+            y = to_numpy(f(torch_dev(x6, dtype), torch_dev(w6, dtype)))
+            assert "stencil_walk" in disco.kernel_timing_read()
+            disco.kernel_timing(False)
+            _, dw = g(plan, torch_dev(x6, dtype), torch_dev(w6, dtype), torch_dev(dy6, dtype))
+            ref = run_oracle(args6, x6, oracle.depthwise_weights(w6.astype(np.float64)), op, basis=2)
+            full = oracle.default().weight_grad(*args6, x6.astype(np.float64), dy6.astype(np.float64),
+                                                transpose=op == "transpose", basis=2)
+            tol = 1e-5 if dtype == "fp32" else 1e-2
+            check("ring walk %dx%d->%dx%d %s %s" % (a6, b6, c6, d6, op, dtype), rel_l2(y, ref), tol)
+            check("  its weight gradient", rel_l2(to_numpy(dw), np.stack([full[i, i] for i in range(3)])), tol)
+            plan.close()
+    del os.environ["DISCO_SPECTRAL_MIN_ENTRIES"]
+    # bf16, stride 2 and 4: the matrix-core kernel's natural pairs, up to 64 output
+    # channels per workgroup.
+    for case7, chans in (((256, 64, 128, 32), (3, 64)), ((256, 128, 128, 32), (9, 33))):
+        args7 = case7 + (3 * math.pi / case7[2],)
+        x7, w7 = synth.random_inputs(18, (2, chans[0]) + case7[:2], (chans[1], chans[0], 9), dtype="bf16")
+        y, plan = run_gpu(args7, x7, w7, "forward", dtype="bf16", algo="matrix_core")
+        check("3x3 bf16 %dx%d->%dx%d matrix_core pairs" % case7, rel_l2(y, run_oracle(args7, x7, w7, "forward")), 2e-2)
+        plan.close()
     n = disco.debug_bounds_violations()
     say("range-check failures: %d kernel files" % n)
     assert n == 0

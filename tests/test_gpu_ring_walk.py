@@ -270,3 +270,150 @@ def test_size_lines_are_a_plans_own(monkeypatch):
     assert "stencil_blocked" in ran and "stencil_walk" not in ran
     assert torch.equal(y0, y1)
     plan.close()
+
+
+# Grids whose wide rings have no tables (no power of two): the blocked kernel
+# sums them beside the walk.
+BLOCKED = [
+    (45, 90, 45, 90, "forward"),        # one ragged tile
+    (60, 450, 60, 450, "forward"),      # two tiles, nq % 4 = 2: single outputs per store, the seam at an odd place
+    (33, 300, 33, 300, "forward"),
+    (90, 362, 45, 181, "transpose"),    # two phases, nq odd
+    (60, 600, 60, 150, "transpose"),    # four phases
+]
+
+
+@pytest.mark.parametrize("basis", list(K))
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("case", BLOCKED, ids=lambda c: "%dx%d_%dx%d_%s" % c)
+def test_walk_beside_the_blocked_kernel(case, dtype, basis, monkeypatch):
+    """Every output against the oracle: up to 7 x 300 fp32 products per output, or
+    the output's rounding to bf16."""
+    import oracle
+    import torch
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "64")  # and lifts the lines on sizes
+    a, b, c, d, op = case
+    # Narrower windows on the stretched grids, whose rings would all be wide.
+    args = (a, b, c, d, (3 if b < 6 * a else 1.5) * math.pi / min(a, c))
+    xs = (2, 3, a, b) if op == "forward" else (2, 3, c, d)
+    x, w = synth.random_inputs(79, xs, (3, K[basis]), dtype=dtype, c_in=1)
+    say("walk beside blocked", case, basis, dtype)
+    plan = disco.Plan(*args, basis=basis)
+    f = plan.forward_depthwise if op == "forward" else plan.transpose_depthwise
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    y = f(torch_dev(x, dtype), torch_dev(w, dtype))
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    assert "stencil_walk" in ran and "stencil_blocked" in ran and "spectral_mac" not in ran
+    ref = run_oracle(args, x, oracle.depthwise_weights(w.astype(np.float64)), op, basis=list(K).index(basis))
+    err = rel_l2(to_numpy(y), ref)
+    mx = np.abs(to_numpy(y) - ref).max() / np.abs(ref).max()
+    say("  rel_l2 %.3e max %.3e" % (err, mx))
+    assert err <= (1e-6 if dtype == "fp32" else 4e-3)
+    assert mx <= (4e-6 if dtype == "fp32" else 8e-3)
+    plan.close()
+
+
+@pytest.mark.parametrize("items,spectral", [(31, None), (32, False), (63, False), (64, True)])
+def test_lines_on_sizes(items, spectral):
+    """256 x 512, default lines: the blocked kernel alone below 2^22 outputs, the
+    walk beside it below 2^23, the walk beside the spectral rings from there on;
+    each item equals itself alone to the rounding of the sums."""
+    import torch
+    n = 256
+    plan = disco.Plan(n, 2 * n, n, 2 * n, 3 * math.pi / n, basis="separable4x4")
+    x, w = (torch_dev(v) for v in synth.random_inputs(80, (1, items, n, 2 * n), (items, 16), c_in=1))
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    y = plan.forward_depthwise(x, w)
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    say("lines", items, sorted(ran))
+    assert ("stencil_walk" in ran) == (spectral is not None)
+    assert ("spectral_mac" in ran) == bool(spectral)
+    assert ("stencil_blocked" in ran) == (not spectral)
+    for ch in (0, items - 1):
+        one = plan.forward_depthwise(x[:, ch:ch + 1].contiguous(), w[ch:ch + 1].contiguous())
+        assert rel_l2(to_numpy(y[:, ch]), to_numpy(one[:, 0])) <= 1e-6
+    plan.close()
+
+
+def test_rings_of_8192_longitudes():
+    """The longest rings that the transforms take (66,560 bytes of LDS each): the
+    paper's layer at L = 4096 against direct sums of every ring in full, and
+    against the oracle at pixels of the polar rings."""
+    import torch
+    L = 4096
+    args = (L + 1, 2 * L, L + 1, 2 * L, 3 * math.pi / L)
+    x, w = synth.random_inputs(85, (1, 1, L + 1, 2 * L), (1, 1, 4))
+    xt, wt = torch_dev(x), torch_dev(w)
+    plan = disco.Plan(*args, basis="axisym4", sampling="poles")
+    disco.kernel_timing(True)
+    disco.kernel_timing_read()
+    y = plan.forward(xt, wt)
+    torch.cuda.synchronize()
+    ran = disco.kernel_timing_read()
+    disco.kernel_timing(False)
+    assert "spectral_irfft" in ran and "stencil_walk" in ran
+    plan.close()
+    direct = disco.Plan(*args, basis="axisym4", sampling="poles", direct=True)
+    z = direct.forward(xt, wt)
+    err = float((y - z).double().norm() / z.double().norm())
+    rings = ((y - z).abs().amax(3) / z.abs().amax(3))[0, 0].amax().item()
+    direct.close()
+    pix = np.array([t * 2 * L + p for t in (0, 1, 5, 40, L - 3, L) for p in (0, 1, 4095, 8191)])
+    ref = run_oracle(args, x, w, "forward", pix=pix, basis=1, sampling=1)
+    got = to_numpy(y).reshape(1, 1, -1)[:, :, pix]
+    say("L = 4096: rel_l2 %.3e against direct sums (largest of a ring %.3e), %.3e against the oracle" %
+        (err, rings, rel_l2(got, ref)))
+    assert err <= 1e-6 and rings <= 1e-5
+    assert rel_l2(got, ref) <= 1e-6
+
+
+@pytest.mark.parametrize("transpose", [False, True], ids=["forward", "transpose"])
+@pytest.mark.parametrize("case", [(64, 128, 32, 64), (32, 64, 64, 128), (64, 256, 32, 64)],
+                         ids=lambda c: "%dx%d_%dx%d" % c)
+@pytest.mark.parametrize("min_entries", [24, 64])
+def test_gradients_between_two_ring_lengths(case, transpose, min_entries, monkeypatch):
+    """Full channel mixing: dx through the adjoint op's spectral rings, dW through
+    the gathered sums of two ring lengths in the frequency domain, against
+    the oracle in full."""
+    import oracle
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", str(min_entries))
+    a, b, c, d = case
+    tc = 3 * math.pi / min(a, c)
+    r = np.random.default_rng(86)
+    C1, C2 = 3, 5
+    xs, ys = ((2, C1, c, d), (2, C2, a, b)) if transpose else ((2, C1, a, b), (2, C2, c, d))
+    x, dy = (r.standard_normal(s).astype(np.float32) for s in (xs, ys))
+    w = (r.standard_normal((C1, C2, 9) if transpose else (C2, C1, 9)) / 5).astype(np.float32)
+    say("gradients between two ring lengths", case, transpose, min_entries)
+    plan = disco.Plan(a, b, c, d, tc, backward=True)
+    assert plan.info()["spectral_rings_%s" % ("transpose" if transpose else "forward")] > 0
+    fn = disco.transpose_backward if transpose else disco.forward_backward
+    dx, dw = fn(plan, torch_dev(x), torch_dev(w), torch_dev(dy))
+    o = oracle.default()
+    rdx = o.input_grad(a, b, c, d, tc, dy.astype(np.float64), w.astype(np.float64), transpose=transpose)
+    rdw = o.weight_grad(a, b, c, d, tc, x.astype(np.float64), dy.astype(np.float64), transpose=transpose)
+    ex, ew = rel_l2(to_numpy(dx), rdx), rel_l2(to_numpy(dw), rdw)
+    say("  dx rel_l2 %.3e dw rel_l2 %.3e" % (ex, ew))
+    assert ex <= 1e-5 and ew <= 1e-5
+    plan.close()
+
+
+@pytest.mark.parametrize("op", ["forward", "transpose"])
+@pytest.mark.parametrize("case", [(64, 128, 32, 64), (32, 64, 64, 128)], ids=lambda c: "%dx%d_%dx%d" % c)
+def test_gathered_sums_of_two_ring_lengths(case, op, monkeypatch):
+    monkeypatch.setenv("DISCO_SPECTRAL_MIN_ENTRIES", "24")
+    a, b, c, d = case
+    args = (a, b, c, d, 3 * math.pi / min(a, c))
+    xs, ws = ((2, 3, a, b), (5, 3, 9)) if op == "forward" else ((2, 3, c, d), (3, 5, 9))
+    x, w = synth.random_inputs(87, xs, ws)
+    say("gathered sums of two ring lengths", case, op)
+    y, plan = run_gpu(args, x, w, op, algo="gather_then_contract")
+    assert plan.info()["spectral_rings_%s" % op] > 0
+    assert rel_l2(y, run_oracle(args, x, w, op)) <= 1e-5
+    plan.close()
