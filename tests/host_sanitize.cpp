@@ -39,82 +39,176 @@ uint16_t bf16_of(float f) {
 }
 
 // Spectral tables: every pair's frequency-domain psi rows, read as the
-// product kernel reads them (its table, rows a = 0 and a = 2 exchanged for an
-// equator mirror), equal the DFT of the pair's own entries at a few
-// frequencies, evaluated directly in fp64; and when the spectral rings are
-// symmetric about the equator, every pair of the southern half reads a
-// northern table.
+// product kernels read them (its table, rows exchanged for an equator mirror),
+// equal the DFT of the pair's own entries on the finer of the two longitude
+// grids at a few frequencies, evaluated directly in fp64, for every basis and
+// op between two ring lengths; when the spectral rings are symmetric about the
+// equator, every pair of the southern half reads a northern table; and the
+// rings' entry list holds their entries in order.
 void check_spectral(const HostOp& op, const SpectralHost& sp, const std::string& what) {
     if (sp.rings.empty()) return;
-    const int N = sp.N, M = sp.M;
+    const OpGeom& g = op.g;
+    const int N = sp.N, M = sp.M, K = basis_size(op.basis);
     const double pi = 3.14159265358979323846;
-    size_t p = 0;
-    int south = 0;
-    std::vector<uint8_t> is_heavy((size_t)op.g.nlat_o, 0);
+    const CellMap cm = cell_map(op.basis);
+    if (N != std::max(g.nlon_i, g.nlon_o) || sp.Ni != g.nlon_i || sp.No != g.nlon_o || M != N / 2 || sp.nv != K) {
+        std::printf("FAIL %s: spectral ring lengths\n", what.c_str());
+        ++failures;
+        return;
+    }
+    // Rows per frequency: part 0 the real, 1 the imaginary part of function k's
+    // DFT; the row that an equator mirror reads instead.
+    struct Row { int k, part, mirror; };
+    std::vector<Row> rows;
+    for (int a = 0; a < (op.basis == DISCO_BASIS_BILINEAR_3X3 ? 3 : 4); ++a)
+        switch (op.basis) {
+            case DISCO_BASIS_BILINEAR_3X3:
+                for (int j = 0; j < 3; ++j) rows.push_back({3 * a + (j == 2), j == 1, 3 * (2 - a) + j});
+                break;
+            case DISCO_BASIS_AXISYMMETRIC_4: rows.push_back({a, 0, a}); break;
+            default:
+                rows.push_back({4 * a, 0, 4 * a + 3});
+                rows.push_back({4 * a + 1, 0, 4 * a + 1});
+                rows.push_back({4 * a + 1, 1, 4 * a + 2});
+                rows.push_back({4 * a + 2, 0, 4 * a});
+        }
+    size_t p = 0, ent = 0;
+    int south = 0, south_pairs = 0;
+    std::vector<uint8_t> is_heavy((size_t)g.nlat_o, 0);
     for (int32_t to : sp.rings) is_heavy[(size_t)to] = 1;
     bool symmetric = true;
-    for (int t = 0; t < op.g.nlat_o; ++t) symmetric &= is_heavy[(size_t)t] == is_heavy[(size_t)(op.g.nlat_o - 1 - t)];
-    for (int32_t to : sp.rings) {
-        const int32_t e1 = op.pat_ptr[(size_t)to + 1];
-        for (int32_t e = op.pat_ptr[(size_t)to]; e < e1; ++p) {
-            const int32_t ti = op.t_in[(size_t)e];
-            int32_t eend = e;
-            while (eend < e1 && op.t_in[(size_t)eend] == ti) ++eend;
-            if (p >= sp.pair_tab.size()) {
-                std::printf("FAIL %s: spectral pair table too short\n", what.c_str());
-                ++failures;
-                return;
+    for (int t = 0; t < g.nlat_o; ++t) symmetric &= is_heavy[(size_t)t] == is_heavy[(size_t)(g.nlat_o - 1 - t)];
+    if (sp.ent_ptr.size() != sp.rings.size() * g.P + 1 || (size_t)sp.ent_ptr.back() != sp.ents.size()) {
+        std::printf("FAIL %s: spectral rings' entry list\n", what.c_str());
+        ++failures;
+        return;
+    }
+    for (size_t h = 0; h < sp.rings.size(); ++h) {
+        const int32_t to = sp.rings[h];
+        // Lags and values of the ring's entries by input ring.
+        std::map<int32_t, std::vector<std::pair<int, std::vector<double>>>> by_ring;
+        for (int r = 0; r < g.P; ++r) {
+            const int pat = to * g.P + r;
+            if (sp.ent_ptr[h * g.P + r] != (int32_t)ent) ++failures;
+            for (int32_t e = op.pat_ptr[(size_t)pat]; e < op.pat_ptr[(size_t)pat + 1]; ++e, ++ent) {
+                int cell = 0;
+                float cv[4];
+                (void)entry_cell_values(op, e, &cell, cv);
+                const RingEntry& E = sp.ents[ent];
+                if (E.row != op.t_in[(size_t)e] * g.nlon_i || E.d != op.d[(size_t)e] || E.cell != cell ||
+                    std::memcmp(E.v, cv, sizeof(cv)) != 0) {
+                    std::printf("FAIL %s: spectral ring %d, entry %zu differs from the op's\n", what.c_str(), to, ent);
+                    ++failures;
+                    return;
+                }
+                std::vector<double> v((size_t)K, 0.0);
+                const double* src = &op.val64[(size_t)e * kBasis];
+                if (op.basis == DISCO_BASIS_SEPARABLE_4X4) {
+                    for (int m = 0; m < 4; ++m)
+                        if (cm.k[cell][m] >= 0) v[(size_t)cm.k[cell][m]] = src[m];
+                } else {
+                    for (int k = 0; k < K; ++k) v[(size_t)k] = src[k];
+                }
+                by_ring[op.t_in[(size_t)e]].push_back({((g.P * op.d[(size_t)e] - r) % N + N) % N, v});
             }
-            const int32_t tb = sp.pair_tab[p];
-            const int32_t tab = tb & 0x7fffffff, r0 = tb < 0 ? 6 : 0;
-            if (tab >= sp.n_tables || (size_t)(tab + 1) * 9 * (M + 1) > sp.vs.size()) {
+        }
+        if (sp.pair_ptr[h] != (int32_t)p || sp.pair_ptr[h + 1] - sp.pair_ptr[h] != (int32_t)by_ring.size()) {
+            std::printf("FAIL %s: pairs of ring %d\n", what.c_str(), to);
+            ++failures;
+            return;
+        }
+        for (const auto& kv : by_ring) {
+            const int32_t ti = kv.first, tb = sp.pair_tab[p], tab = tb & 0x7fffffff;
+            if (tab >= sp.n_tables || (size_t)(tab + 1) * K * (M + 1) > sp.vs.size() ||
+                sp.slot_ring[(size_t)sp.pair_slot[p]] != ti) {
                 std::printf("FAIL %s: pair %zu reads table %d of %d\n", what.c_str(), p, tab, sp.n_tables);
                 ++failures;
                 return;
             }
-            if (to > op.g.nlat_o - 1 - to) south += tb < 0;
+            // (A separable filter's direction at its own centre is south on both
+            // sides of the equator: that pair is no mirror of another.)
+            const bool centre = op.basis == DISCO_BASIS_SEPARABLE_4X4 && g.nlat_i == g.nlat_o && ti == to;
+            if (to > g.nlat_o - 1 - to) {
+                south += tb < 0;
+                south_pairs += !centre;
+            }
             double scale = 0.0;
-            for (int32_t k = e; k < eend; ++k)
-                for (int kk = 0; kk < kBasis; ++kk) scale += std::fabs(op.val64[(size_t)k * kBasis + kk]);
+            for (const auto& l : kv.second)
+                for (double x : l.second) scale += std::fabs(x);
             scale /= N;
             for (int m : {0, 1, M / 3, M}) {
-                for (int a = 0; a < 3; ++a) {
-                    double re0 = 0, im0 = 0, re1 = 0;
-                    for (int32_t k = e; k < eend; ++k) {
-                        const double ang = -2.0 * pi * (double)m * op.d[(size_t)k] / N;
-                        re0 += op.val64[(size_t)k * kBasis + 3 * a] * std::cos(ang);
-                        im0 += op.val64[(size_t)k * kBasis + 3 * a] * std::sin(ang);
-                        re1 += op.val64[(size_t)k * kBasis + 3 * a + 1] * std::cos(ang);
+                for (size_t row = 0; row < rows.size(); ++row) {
+                    double want = 0.0;
+                    for (const auto& l : kv.second) {
+                        const double ang = -2.0 * pi * (double)m * l.first / N;
+                        want += l.second[(size_t)rows[row].k] * (rows[row].part ? std::sin(ang) : std::cos(ang));
                     }
-                    const int row = a == 0 ? r0 : a == 2 ? 6 - r0 : 3;
-                    const float* v = &sp.vs[(size_t)tab * 9 * (M + 1)];
-                    const double got[3] = {v[(size_t)(row + 0) * (M + 1) + m], v[(size_t)(row + 1) * (M + 1) + m],
-                                           v[(size_t)(row + 2) * (M + 1) + m]};
-                    const double want[3] = {re0 / N, im0 / N, re1 / N};
-                    for (int j = 0; j < 3; ++j)
-                        if (std::fabs(got[j] - want[j]) > 1e-6 * scale + 1e-30) {
-                            std::printf("FAIL %s: pair %zu (rings %d, %d) row %d freq %d: table %.9g, DFT %.9g\n",
-                                        what.c_str(), p, to, ti, 3 * a + j, m, got[j], want[j]);
-                            ++failures;
-                            return;
-                        }
+                    want /= N;
+                    const int at = tb < 0 ? rows[row].mirror : (int)row;
+                    const double got = sp.vs[((size_t)tab * K + at) * (M + 1) + m];
+                    if (std::fabs(got - want) > 1e-6 * scale + 1e-30) {
+                        std::printf("FAIL %s: pair %zu (rings %d, %d) row %zu freq %d: table %.9g, DFT %.9g\n",
+                                    what.c_str(), p, to, ti, row, m, got, want);
+                        ++failures;
+                        return;
+                    }
                 }
             }
-            e = eend;
+            ++p;
         }
     }
     if (p != sp.pair_tab.size()) {
         std::printf("FAIL %s: %zu pairs, table of %zu\n", what.c_str(), p, sp.pair_tab.size());
         ++failures;
     }
-    int south_pairs = 0;
-    for (size_t r = 0; r < sp.rings.size(); ++r)
-        if (sp.rings[r] > op.g.nlat_o - 1 - sp.rings[r]) south_pairs += sp.pair_ptr[r + 1] - sp.pair_ptr[r];
     if (symmetric && south != south_pairs) {
         std::printf("FAIL %s: %d of %d southern spectral pairs share a northern table\n", what.c_str(), south,
                     south_pairs);
         ++failures;
     }
+}
+
+// The blocked layout with wide patterns apart: the same stored values as without,
+// the wide patterns' work items and split patterns last and on their own, every
+// pattern's segments in one run, its slots in order.
+void check_stencil_split(const HostOp& op, int tile, int min_entries, const std::string& what) {
+    const std::vector<uint8_t> wide = wide_patterns(op, min_entries);
+    StencilHost A, B;
+    std::string err;
+    check(pack_stencil(op, 256, tile, &A, &err), what + " pack_stencil", err);
+    check(pack_stencil(op, 256, tile, &B, &err, wide), what + " pack_stencil (wide apart)", err);
+    auto fail = [&](const char* m) {
+        std::printf("FAIL %s: blocked layout with wide patterns apart: %s\n", what.c_str(), m);
+        ++failures;
+    };
+    auto sum = [](const StencilHost& H) {
+        double t = 0;
+        for (const PVal& v : H.vals)
+            for (float x : v.v) t += x;
+        return t;
+    };
+    if (A.vals.size() != B.vals.size() || A.segs.size() != B.segs.size() || A.n_slots != B.n_slots ||
+        std::fabs(sum(A) - sum(B)) > 1e-9 * std::fabs(sum(A)))
+        return fail("stored values differ");
+    std::vector<int> segs((size_t)op.g.n_patterns(), 0);
+    int prev = 0;
+    for (size_t i = 0; i < B.items.size(); ++i) {
+        if (B.items[i].seg_begin != prev || B.items[i].seg_end <= prev) return fail("work items do not cover the segments");
+        prev = B.items[i].seg_end;
+        for (int s = B.items[i].seg_begin; s < B.items[i].seg_end; ++s) {
+            if ((bool)wide[(size_t)B.segs[(size_t)s].pattern] != ((int)i >= B.n_items_light)) return fail("a wide pattern among the others");
+            ++segs[(size_t)B.segs[(size_t)s].pattern];
+        }
+    }
+    if (prev != (int)B.segs.size()) return fail("segments without a work item");
+    for (size_t k = 0; k < B.red_pattern.size(); ++k) {
+        const int pat = B.red_pattern[k];
+        if ((bool)wide[(size_t)pat] != ((int)k >= B.n_split_light)) return fail("a wide split pattern among the others");
+        if (B.red_ptr[k + 1] - B.red_ptr[k] != segs[(size_t)pat] || segs[(size_t)pat] < 2) return fail("slots of a split pattern");
+        segs[(size_t)pat] = 1;
+    }
+    for (int n : segs)
+        if (n != 1) return fail("a pattern without segments, or split without a reduction");
 }
 
 // The matrix-core layout holds every entry's nine values (rounded to bf16)
@@ -415,8 +509,27 @@ void run_op(const PlanParams& p, bool transpose, bool quad_at_output, const char
             StencilHost S;
             check(pack_stencil(op, 256, tile, &S, &err), what + " pack_stencil", err);
         }
+        for (int tile : {kStencilSmallTile, kStencilTile})
+            for (int n : {32, 128}) check_stencil_split(op, tile, n, what);
         check_walk(op, 128, what);
         check_walk(op, 32, what + " (32 entries)");
+    }
+    // Every basis and op between two ring lengths; the 3x3 basis's own lines below.
+    for (int n : {16, 192}) {
+        SpectralHost sp;
+        std::vector<uint8_t> heavy;
+        check(build_spectral(op, n, &sp, &heavy, &err, true), what + " build_spectral (phases)", err);
+        check_spectral(op, sp, what + (n == 16 ? " (16 entries, phases)" : " (192 entries, phases)"));
+        if (!sp.rings.empty()) {  // over its bound: none at all
+            SpectralHost none;
+            check(build_spectral(op, n, &none, &heavy, &err, true, (int64_t)sp.vs.size() * 4 - 1), what + " build_spectral (bound)", err);
+            bool any = !none.rings.empty() || !none.vs.empty();
+            for (uint8_t h : heavy) any |= h != 0;
+            if (any) {
+                std::printf("FAIL %s: tables past their bound\n", what.c_str());
+                ++failures;
+            }
+        }
     }
     if (op.basis != DISCO_BASIS_BILINEAR_3X3) return;
     check_mfma(op, what);
