@@ -140,7 +140,7 @@ typedef struct {
  * whole-pixel longitude shifts, as without the flag on small calls only.  The
  * plan holds no frequency-domain tables; large calls are slower (2048 x 4096,
  * 8 separable depthwise channels: 0.67 against 0.27 ms). */
-enum { DISCO_PLAN_BACKWARD = 1, DISCO_PLAN_EAGER = 2, DISCO_PLAN_DIRECT = 4 };
+enum { DISCO_PLAN_BACKWARD = 1, DISCO_PLAN_EAGER = 2, DISCO_PLAN_DIRECT = 8 };
 
 typedef struct {
     void* data;       /* device pointer (may be NULL only when the tensor is empty) */

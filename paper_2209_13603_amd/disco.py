@@ -39,7 +39,7 @@ BASIS_SIZE = {DISCO_BASIS_BILINEAR_3X3: 9, DISCO_BASIS_AXISYMMETRIC_4: 4, DISCO_
 SAMPLINGS = {"cell_centred": DISCO_SAMPLING_CELL_CENTRED, "poles": DISCO_SAMPLING_POLES}
 DISCO_PLAN_BACKWARD = 1
 DISCO_PLAN_EAGER = 2
-DISCO_PLAN_DIRECT = 4
+DISCO_PLAN_DIRECT = 8
 
 ALGO_AUTO = 0
 ALGO_GATHER_THEN_CONTRACT = 1

@@ -68,7 +68,7 @@ def test_basis_validation():
     assert rc == disco.DISCO_ERR_UNSUPPORTED
     rc, _ = _create(32, 64, 32, 64, 0.3, basis=disco.Basis(0, 0, -0.1))
     assert rc == disco.DISCO_ERR_INVALID_ARGUMENT
-    rc, _ = _create(32, 64, 32, 64, 0.3, basis=disco.Basis(0, 0, 0.0, 0, 8))
+    rc, _ = _create(32, 64, 32, 64, 0.3, basis=disco.Basis(0, 0, 0.0, 0, 16))
     assert rc == disco.DISCO_ERR_INVALID_ARGUMENT  # unknown flag
     lib = disco.library()
     assert lib.disco_plan_create(32, 64, 32, 64, 0.3, None, None) == disco.DISCO_ERR_INVALID_ARGUMENT
