@@ -398,8 +398,9 @@ int32_t disco_debug_bounds_violations(void);
  * "stencil", "stencil_blocked" and "stencil_walk" rows of the axisymmetric and separable
  * bases, whose psi has W folded in, the (output pixel, input pixel) pairs
  * instead; with these two bases a depthwise call runs the rows of
- * c_in = c_out = 1 once per channel, and the rows are those of a call of
- * eight items or more).  A kernel
+ * c_in = c_out = 1 once per channel, and, since the kernels of large calls
+ * depend on the number of items, the rows are those of one item of the
+ * axisymmetric basis and of 32 items of the separable one).  A kernel
  * that only moves intermediate data reports zeros where it touches neither
  * x nor y.  Up to `capacity` rows are written (any output pointer may be
  * NULL) and *count receives the number of kernels.  Host only, no device

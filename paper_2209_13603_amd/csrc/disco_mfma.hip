@@ -319,12 +319,13 @@ __global__ __launch_bounds__(kMfmaTile, 2) void k_mfma(const MSeg* __restrict__ 
 // four dwords from (its group's offset) / 2 on: staging is a plain copy of 16
 // bytes per 8 inputs, and a segment is the whole output ring but near the
 // poles, so y is written once in bf16, with few partial outputs to reduce.
-// 52.5 KB of LDS lets three workgroups share a CU for up to 32 output channels
+// 50.3 KB of LDS lets three workgroups share a CU for up to 32 output channels
 // (two with 64 KB: 512 x 1024 -> 256 x 512, 20 -> 30 channels, 4 items, 207 ->
 // 176 us; with 64 output channels the registers allow two).  Bound by the
 // gather's LDS reads, 64 clocks per chunk and wave.  That op: 495 -> 176 us,
-// with 32 -> 64 channels 1141 -> 335 us; loads through buffers instead of
-// guarded ones took the latter from 375 us.
+// with 32 -> 64 channels 1141 -> 335 us repeated on the same buffers, 357 us on
+// new ones each time; loads through buffers instead of guarded ones took
+// it from 375 us (the same buffers).
 constexpr int kPairDw = kMfmaPairElems / 2;      // LDS dwords per staged channel
 constexpr int kPairBlocks = kMfmaPairElems / 8;  // 8-input blocks per channel
 constexpr int kPairItems = kPairBlocks / kMfmaTile;  // blocks of each channel per thread

@@ -694,7 +694,11 @@ __global__ __launch_bounds__(kFftBlock) void k_irfft_rings(const int32_t* __rest
     }
     const int N = 2 * M;
     const int64_t base = (((int64_t)b * Co + co) * nlat_o + rings[h]) * N;
-    if (__syncthreads_or(!fine) && R.ptr) return ring_direct(R, h, b, co, y + base, N);
+    if (R.ptr) {
+        if (__syncthreads_or(!fine)) return ring_direct(R, h, b, co, y + base, N);
+    } else {
+        __syncthreads();
+    }
     const float2* z = fft_lds(a, bb, M, thi, tlo, true);
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
         const float2 v = z[j];
