@@ -20,12 +20,12 @@
 // Three kernels.  k_stencil_walk takes the one-channel items of stride-1 ops
 // on every ring with narrow windows: it keeps input rings in LDS while it
 // walks output rings.  k_stencil_blocked takes the wide rings beside it (the
-// spectral path does on larger grids) and ops with several input channels
+// spectral path does in larger calls) and ops with several input channels
 // and one output channel; k_stencil the rest.  Alone on one box, 2048 x
-// 4096, eight separable channels: the blocked kernel over every ring 640 us,
-// over the narrow rings 500 us, the walk over the narrow rings 183 us (512
-// MB at 2.8 TB/s; 107 us without its products, which occupy the fp32 matrix
-// cores for about 70 us).
+// 4096, eight separable channels, wide rings from 128 entries on: the blocked
+// kernel over every ring 640 us, over the narrow rings 500 us, the walk over
+// the narrow rings 183 us (512 MB at 2.8 TB/s; 107 us without its products,
+// which occupy the fp32 matrix cores for about 70 us).
 //
 // k_stencil's layout and walk are the packed one of the fused kernel (disco_fused.hip):
 // one workgroup = 256 consecutive output longitudes of one pattern (output
