@@ -79,8 +79,7 @@ def test_lazy_and_eager_plans_agree_bitwise(op, algo):
 def test_folded_bases_hold_spectral_tables_only_where_a_call_reads_them():
     """Separable basis: ops with a longitude stride and cutoffs whose rings are
     all wide have no ring walk, so no call reads frequency-domain tables there
-    and none are built; where the walk holds the windows of five rings of
-    cutoff, only rings from 192 entries on have them."""
+    and none are built."""
     n = 256
     down = disco.Plan(n, 2 * n, n // 2, n, 3 * math.pi / (n // 2), basis="separable4x4", eager=True)
     i = down.info()
@@ -90,38 +89,51 @@ def test_folded_bases_hold_spectral_tables_only_where_a_call_reads_them():
     assert i["spectral_rings_transpose"] > 0
     eight = disco.Plan(n, 2 * n, n, 2 * n, 8 * math.pi / n, basis="separable4x4", eager=True)
     assert eight.info()["spectral_rings_forward"] == 0 and eight.info()["bytes_spectral"] == 0
-    for cut in (3, 5):
-        p = disco.Plan(n, 2 * n, n, 2 * n, cut * math.pi / n, basis="separable4x4")
-        e = disco.psi_entries(n, 2 * n, n, 2 * n, cut * math.pi / n, basis=2)
-        counts = np.bincount(e["out_ring"], minlength=n)
-        i = p.info()
-        say("  %d rings of cutoff: %d spectral rings, %.2f MB of tables" % (cut, i["spectral_rings_forward"],
-                                                                          i["bytes_spectral"] / 1e6))
-        assert i["spectral_rings_forward"] == int((counts >= 192).sum()) > 0
-        p.close()
     down.close()
     eight.close()
 
 
-def test_six_rings_of_cutoff_walk_at_the_lower_line():
-    """Six rings of cutoff: with the line at 192 entries the walk does not hold
-    the windows, so it is drawn at 128; a call past the lines on sizes equals
-    its channels alone (direct sums) to the rounding of two transforms."""
+@pytest.mark.parametrize("n,cut,line", [(256, 3, 128), (256, 5, 128), (256, 6, 128), (1024, 3, 192), (1024, 5, 192),
+                                        (1024, 6, 128)])
+def test_line_of_wide_rings_of_the_folded_bases(n, cut, line):
+    """Wide from 128 entries on, on rings of 2048 longitudes from 192 on, the other
+    of the two where the walk does not hold the windows."""
+    args = (n, 2 * n, n, 2 * n, cut * math.pi / n)
+    plan = disco.Plan(*args, basis="separable4x4")
+    counts = np.bincount(disco.psi_entries(*args, basis=2)["out_ring"], minlength=n)
+    i = plan.info()
+    say("  %d x %d, %d rings of cutoff: %d spectral rings, %.2f MB of tables" %
+        (n, 2 * n, cut, i["spectral_rings_forward"], i["bytes_spectral"] / 1e6))
+    assert i["spectral_rings_forward"] == int((counts >= line).sum()) > 0
+    plan.close()
+
+
+@pytest.mark.parametrize("grids,op,C", [((256, 512, 256, 512), "forward", 65),    # the line at 128
+                                        ((256, 512, 128, 256), "transpose", 65),  # at 192: no walk at 128
+                                        ((1024, 2048, 1024, 2048), "forward", 4)])  # at 128: no walk at 192
+def test_six_rings_of_cutoff(grids, op, C):
+    """Six rings of cutoff on either line: a call past the lines on sizes equals
+    its channels alone, directly summed, to the rounding of two transforms."""
     import torch
-    n, C = 256, 65
-    plan = disco.Plan(n, 2 * n, n, 2 * n, 6 * math.pi / n, basis="separable4x4")
-    x, w = synth.random_inputs(8, (1, C, n, 2 * n), (C, 16), c_in=1)
+    a, b, c, d = grids
+    tc = 6 * math.pi / min(a, c)
+    plan = disco.Plan(*grids, tc, basis="separable4x4")
+    one = disco.Plan(*grids, tc, basis="separable4x4", direct=True)
+    x, w = synth.random_inputs(8, (1, C) + ((a, b) if op == "forward" else (c, d)), (C, 16), c_in=1)
     xt, wt = torch_dev(x), torch_dev(w)
+    f, g = (p.forward_depthwise if op == "forward" else p.transpose_depthwise for p in (plan, one))
     disco.kernel_timing(True)
     disco.kernel_timing_read()
-    y = plan.forward_depthwise(xt, wt)
+    y = f(xt, wt)
+    torch.cuda.synchronize()
     ran = disco.kernel_timing_read()
     disco.kernel_timing(False)
     assert "stencil_walk" in ran and "spectral_mac" in ran
     for ch in (0, C - 1):
-        one = plan.forward_depthwise(xt[:, ch:ch + 1].contiguous(), wt[ch:ch + 1].contiguous())
-        err = float((y[:, ch:ch + 1] - one).norm() / one.norm())
+        z = g(xt[:, ch:ch + 1].contiguous(), wt[ch:ch + 1].contiguous())
+        err = float((y[:, ch:ch + 1] - z).norm() / z.norm())
         say("  channel %d rel_l2 %.3e" % (ch, err))
         assert err <= 1e-6
     torch.cuda.synchronize()
     plan.close()
+    one.close()
