@@ -179,18 +179,18 @@ int fused_target_entries(const HostOp& h, int tile) {
 // for that plan (tests reach every path on small grids that way).  A direct
 // sum feeds all nine functions of the 3x3 basis.  The other bases, whose tables
 // have up to 16 rows and whose direct sums feed one folded filter, draw the
-// line higher on rings of 2048 longitudes and more, where the tables are large,
+// line higher on rings of 1024 longitudes and more, where the tables are large,
 // and take the other of the two where the ring walk does not hold the windows
-// (five or six rings of cutoff).  64 x 128, 1024 separable items, at 128 and
-// 192: 141 and 165 us, 256 x 512, 128 items, 113 and 117 us, 512 x 1024, 32 items,
-// 108 and 109 us, 1024 x 2048 with five rings of cutoff, 8 items, 178 and 160 us;
-// upsampling to 512 x 1024 with six rings, 128 items, 2618 us (no walk) and 517
-// us.  2048 x 4096, 8 separable depthwise
-// channels, at 128 and 192 (the spectral rings on the caller's stream):
+// (five or six rings of cutoff).  At 128 and 192: 64 x 128, 1024 separable
+// items, 141 and 165 us, 256 x 512, 128 items, 113 and 117 us, 512 x 1024, 32
+// items, 108 and 109 us, upsampling to it, 128 items, 227 and 220 us, 1024 x 2048
+// with five rings of cutoff, 8 items, 178 and 160 us; upsampling to 512 x 1024
+// with six rings, 128 items, 2618 us (no walk) and 517 us.  2048 x 4096, 8
+// separable depthwise channels (the spectral rings on the caller's stream):
 // three rings of cutoff 306 us with 104 MB of tables and 313 us with 70 MB,
 // five 580 us with 547 MB and 516 us with 349 MB; six 847 us with 1054 MB and,
 // without a walk, 2242 us; without the tables 677, 1247 and 1858 us.
-constexpr int kWideEntries = 128, kWideEntriesLong = 192, kLongRing = 2048;
+constexpr int kWideEntries = 128, kWideEntriesLong = 192, kLongRing = 1024;
 int wide_line_override() {  // 0: none
     const char* v = std::getenv("DISCO_SPECTRAL_MIN_ENTRIES");
     return v && *v ? std::max(1, std::atoi(v)) : 0;

@@ -93,10 +93,10 @@ def test_folded_bases_hold_spectral_tables_only_where_a_call_reads_them():
     eight.close()
 
 
-@pytest.mark.parametrize("n,cut,line", [(256, 3, 128), (256, 5, 128), (256, 6, 128), (1024, 3, 192), (1024, 5, 192),
+@pytest.mark.parametrize("n,cut,line", [(256, 3, 128), (256, 5, 128), (256, 6, 128), (512, 3, 192), (1024, 3, 192), (1024, 5, 192),
                                         (1024, 6, 128)])
 def test_line_of_wide_rings_of_the_folded_bases(n, cut, line):
-    """Wide from 128 entries on, on rings of 2048 longitudes from 192 on, the other
+    """Wide from 128 entries on, on rings of 1024 longitudes from 192 on, the other
     of the two where the walk does not hold the windows."""
     args = (n, 2 * n, n, 2 * n, cut * math.pi / n)
     plan = disco.Plan(*args, basis="separable4x4")
